@@ -33,8 +33,10 @@ def _hipcc():
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-result"]
 # No packed fp32 ops in device code (v_pk_*_f32 are avoided on this hardware).
+# A kernel's first arguments (up to 14 dwords) arrive in registers instead of through a load
+# that everything else in the kernel waits for.
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-          "-munsafe-fp-atomics"]
+          "-munsafe-fp-atomics", "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def build(verbose=False):

@@ -30,7 +30,7 @@
 //
 // Compute, per wave (32 query columns, one per lane pair), per 32-key sub-block b:
 //   * S^T(b) = K Q^T with v_mfma_f32_32x32x16_bf16: A = K rows from LDS, B = Q held in
-//     registers, so every lane owns one query column and 16 of the sub-block's scores;
+//     registers (read once through the ring's LDS, before its later tiles need it), so every lane owns one query column and 16 of the sub-block's scores;
 //   * online softmax in the exp2 domain against a per-column reference m, set to the exact
 //     max of the item's first sub-block (lane pair combined by v_permlane32_swap); later
 //     probabilities exp2(s c - m) are accumulated against it as they come, so a sub-block
@@ -122,6 +122,12 @@ __device__ inline void lds_dma_b32(const i32x4& rs, uint32_t voff, uint32_t lds)
 // Wait until this wave's LDS operations are complete (before a barrier that publishes them).
 __device__ inline void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
 
+// A dword at a wave-uniform address, by a scalar load (the constant address space asks for one).
+__device__ inline int32_t scalar_load(const int32_t* p) {
+  typedef const __attribute__((address_space(4))) int32_t const_i32;
+  return *reinterpret_cast<const const_i32*>(reinterpret_cast<uintptr_t>(p));
+}
+
 // Sub-block max of the 16 scores a lane holds, then over the lane pair (l, l ^ 32).  The
 // scores come straight from MFMAs: the max must be ordinary code (the compiler forms
 // v_max3 chains), so that the wait states an MFMA result needs before a VALU read are
@@ -169,11 +175,13 @@ struct Ring {
 
 template <bool kFp8, int kColWaves, int kHalves, bool kFused, bool kQ8>
 __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)) void attn_main_kernel(
-    const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
-    void* kpool, void* vpool, const float* __restrict__ kscale,
-    const float* __restrict__ vscale, const int32_t* __restrict__ block_tables, int32_t max_pages, int32_t hq,
-    int32_t hkv, float scale_log2, PlanPtrs pv, int32_t group_by_xcd, const uint16_t* __restrict__ knew,
-    const uint16_t* __restrict__ vnew, int64_t total_rows) {
+    const ItemRec* __restrict__ items, const PlanHeader* __restrict__ hdr, int32_t xcd_items,
+    int32_t max_pages, const int32_t* __restrict__ block_tables, const uint16_t* __restrict__ q, int32_t hq,
+    int32_t G, uint32_t ginv, int32_t tq,   // these fill the preloaded argument registers
+    uint16_t* __restrict__ out, float* __restrict__ lse, void* kpool, void* vpool,
+    const float* __restrict__ kscale, const float* __restrict__ vscale, int32_t hkv, float scale_log2,
+    float* __restrict__ partials, const uint16_t* __restrict__ knew, const uint16_t* __restrict__ vnew,
+    int64_t total_rows) {
   using RingT = Ring<kFp8, kColWaves, kHalves>;
   constexpr int kWaves = kColWaves * kHalves;
   constexpr int kS = RingT::kStages;
@@ -193,18 +201,19 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   // the items cost about the same, consecutive items (one kv head's pages) go to one XCD's
   // L2; otherwise workgroups take items in plan order (longest request first), which the
   // round-robin dispatch spreads evenly over the XCDs.
-  const int w_item = group_by_xcd ? xcd_logical(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const ItemRec it = pv.items[w_item];
-  const int W = pv.hdr->num_items;
-  if (pv.hdr->status != 0) {   // the device plan did not fit this launch: nothing planned
+  const int w_item = xcd_items != 0 ? xcd_logical(blockIdx.x, xcd_items) : (int)blockIdx.x;
+  const ItemRec it = items[w_item];
+  const int W = hdr->num_items, status = hdr->status;
+  // every load is issued before the first branch (left to itself, the compiler loads the item
+  // only after the status has arrived, and the item count after that: two more round trips)
+  __asm__ volatile("" ::"s"(status), "s"(W), "s"(it.r), "s"(it.p), "s"(it.part_off), "s"(kpool), "s"(vpool), "s"(hkv));
+  if (status != 0) {   // the device plan did not fit this launch: nothing planned
     poison_outputs(out, lse, total_rows, hq);
     return;
   }
   if (w_item >= W || it.r < 0) return;   // past the plan's items, or a bin's padding
   const int P = it.p, C = it.c, row0 = it.row0, ns = it.ns, g = it.g;
   const int i0 = it.i0, i1 = it.i1;
-  const int G = hq / hkv;
-  const int tq = tile_tokens(G, 32 * kColWaves);
   const int32_t* bt = block_tables + (int64_t)it.r * max_pages;
 
   const int lane = threadIdx.x & 63;
@@ -224,8 +233,10 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   const int grp_base = grp * RingT::kGroupBytes;
   constexpr int kKBase = 0;
   constexpr int kVBase = kS * kTileBytes;
-  const int tok = i0 + col / G;
-  const int hq_col = g * G + col % G;
+  // c / G = (c ginv) >> 24 exactly for c < 256 and G < 2^16
+  auto div_g = [&](int c) { return (int)(((uint32_t)c * ginv) >> 24); };
+  const int tok = i0 + div_g(col);
+  const int hq_col = g * G + col - div_g(col) * G;
   const bool valid = col < tq * G && tok < i1;
   const int horizon = valid ? P + tok : P + i1 - 1;   // last visible key of this column
 
@@ -236,6 +247,15 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
     v_mul = vscale[g];
   }
 
+  // Page ids of this wave's page of the first tiles, by scalar loads that are in flight with
+  // the Q loads (entry lo/16 + 4 j + pw of the table, clamped to the item's last page, whose
+  // entry exists: a tile past the range is copied with a size-0 descriptor).
+  const int pw = cw / kQuarters;
+  const int last_page = hi > lo ? (hi - 1) >> 4 : (it.hi > it.lo ? (it.hi - 1) >> 4 : 0);
+  int32_t pg[kS + 1];
+#pragma unroll
+  for (int j = 0; j <= kS; ++j) pg[j] = scalar_load(bt + min((lo >> 4) + 4 * j + pw, last_page));
+
   // Q^T operand: lane (n, half) holds Q[col][16 ks + 8 half .. +7] for ks = 0..7.
   bf16x8 qf[8];
   // kQ8: the column quantised to e4m3 with its own scale sq = max |Q[col]| / 448 (1 for a
@@ -243,7 +263,9 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   // encoder); for the fp8 MFMA of k-half j lane (n, half) holds the codes of
   // Q[col][32 (2 j + half) + b], b < 32, and the scores take sq in their scale.
   i32x8 q8[2];
-  if constexpr (!kQ8) {
+  if constexpr (!kFp8) {
+    // copied through LDS below, so that its latency overlaps that of the first K and V tiles
+  } else if constexpr (!kQ8) {
     const uint16_t* qrow = q + ((int64_t)(row0 + (valid ? tok : 0)) * hq + (valid ? hq_col : 0)) * 128 + 8 * half;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
@@ -314,7 +336,6 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   }
 
   // Tile loads: column wave cw moves rows [s0, s0 + kRowsPerWave) of page pw of each tile.
-  const int pw = cw / kQuarters;
   const int s0 = (cw % kQuarters) * kRowsPerWave;
   uint32_t kvo[kFp8 ? kF8Loads : kDma], vvo[kFp8 ? kF8Loads : kDma];
   // Fused append (bf16, page-aligned prefixes): keys at or past P, the chunk's own, are
@@ -349,21 +370,18 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   const int64_t page_stride = (int64_t)hkv * kRun;
 
   const int ntiles = nt0;                            // tile steps (the same in both groups)
-  const int last_page = hi > lo ? (hi - 1) >> 4 : (it.hi > it.lo ? (it.hi - 1) >> 4 : 0);
   // Page ids.  Lane l of pg_win holds the physical page of this wave's page of tile
-  // win0 + l (block-table entry lo/16 + 4 (win0 + l) + pw, clamped to the item's last
-  // page, whose entry exists: a tile past the range is copied with a size-0 descriptor).
-  // The next 64-tile window is copied into this wave's LDS slot 64 tiles before it is
-  // needed, by an LDS-direct load that the per-iteration vmcnt waits cover (it is older than
-  // the copies they wait for), and read into pg_win when the window moves on.  Page ids
-  // never come from scalar loads inside the loop: those share lgkmcnt with the LDS reads,
+  // win0 + l (clamped as above).  Each 64-tile window is copied into one of this wave's two
+  // LDS slots (the first into slot 1) by an LDS-direct load, 64 tiles before it is needed for
+  // all but the first; the per-iteration vmcnt waits cover it (it is older than the copies
+  // they wait for), and it is read into pg_win when the window moves on.  Page ids never come from scalar loads inside the loop: those share lgkmcnt with the LDS reads,
   // whose waits would then all be full waits.
   const i32x4 bt_rs = sgpr_rsrc(bt, 4 * (last_page + 1));
   auto win_offset = [&](int w0) -> uint32_t {
     const int idx = (lo >> 4) + 4 * (w0 + lane) + pw;
     return 4u * (uint32_t)(idx < last_page ? idx : last_page);
   };
-  int32_t pg_win = bt[(win_offset(0) >> 2)];     // tracked load, waited for with the Q loads
+  int32_t pg_win = 0;
   int win0 = 0, win_slot = 0;
   auto fetch_window = [&](int w0, int slot) {
     lds_dma_b32(bt_rs, win_offset(w0),
@@ -698,59 +716,122 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
 
   // Fused append: the first key-range piece of each (kv head, query tile) writes the tile's
   // chunk rows of kv head g into their pages (slots P + i, i in [i0, i1)); nothing in this
-  // launch reads those slots from the pages.  Its loads and stores overlap the Q loads and
-  // are covered by the wait below.
-  if (kFused && it.s == 0) {
-    constexpr int kThreads = kWaves * 64;
-    const int units = (i1 - i0) * 2 * 16;   // (token, K or V, 16-byte chunk)
-    for (int u = threadIdx.x; u < units; u += kThreads) {
-      const int c = u & 15, kv = (u >> 4) & 1, i = i0 + (u >> 5);
-      const int pos = P + i;
-      const int64_t page = bt[pos >> 4];
-      const uint16_t* src = (kv ? vnew : knew) + ((int64_t)(row0 + i) * hkv + g) * kHeadDim + 8 * c;
-      char* dst = static_cast<char*>(kv ? vpool : kpool) +
-                  ((page * hkv + g) * 16 + (pos & 15)) * kRowBytes + 16 * c;
-      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(src);
+  // launch reads those slots from the pages.  Unit u is 16-byte chunk u % 16 of the K (u / 16
+  // even) or V row of token i0 + u / 32.  The first kAppend units of each thread are loaded
+  // ahead of the tile copies and stored once the first tiles have arrived.
+  constexpr int kThreads = kWaves * 64;
+  constexpr int kAppend = 4;
+  const int units = kFused && it.s == 0 ? (i1 - i0) * 32 : 0;
+  auto append_src = [&](int u) {
+    const uint16_t* src = ((u >> 4) & 1 ? vnew : knew) + ((int64_t)(row0 + i0 + (u >> 5)) * hkv + g) * kHeadDim;
+    return *reinterpret_cast<const u32x4*>(src + 8 * (u & 15));
+  };
+  auto append_dst = [&](int u, int64_t page) {
+    const int slot = (P + i0 + (u >> 5)) & 15;
+    return reinterpret_cast<u32x4*>(static_cast<char*>((u >> 4) & 1 ? vpool : kpool) +
+                                    ((page * hkv + g) * 16 + slot) * kRowBytes + 16 * (u & 15));
+  };
+  u32x4 ax[kFused ? kAppend : 1];
+  int32_t apage[kFused ? kAppend : 1];
+  if constexpr (kFused) {
+#pragma unroll
+    for (int k = 0; k < kAppend; ++k) {
+      const int u = (int)threadIdx.x + k * kThreads;
+      if (u < units) {
+        apage[k] = bt[(P + i0 + (u >> 5)) >> 4];
+        ax[k] = append_src(u);
+      }
     }
   }
-
-  // Page ids of the first tiles are requested while the Q loads are in flight; the Q loads
-  // are then waited for on every path, before any LDS-direct copy is issued: the compiler's
-  // wait-count bookkeeping does not see those copies, and a Q load it still counted as
-  // pending would make it wait for every copy in each step of the loop.
-  wait_vmcnt<0>();
-  int32_t pg[kS + 1];
+  auto append_rows = [&]() {
+    if constexpr (kFused) {
+      wait_vmcnt<0>();   // on every path: a load that the compiler still counted as pending
+                         // would make it wait for the tile copies in each step of the loop
 #pragma unroll
-  for (int j = 0; j <= kS; ++j) pg[j] = page_of(j);
-  if (ntiles > 64 - kS - 2) fetch_window(64, 0);
+      for (int k = 0; k < kAppend; ++k) {
+        const int u = (int)threadIdx.x + k * kThreads;
+        if (u < units) *append_dst(u, apage[k]) = ax[k];
+      }
+      for (int u = (int)threadIdx.x + kAppend * kThreads; u < units; u += kThreads)
+        *append_dst(u, bt[(P + i0 + (u >> 5)) >> 4]) = append_src(u);
+    }
+  };
 
   if (ntiles > 0) {
-    // Prologue: copies K(0), V(0), K(1), V(1), ..., K(kS - 2), V(kS - 2), K(kS - 1); waits
-    // for K(0); sub-block 0 sets the reference to its own max (a lane with no visible key
-    // there has none in the group's range, as its visible keys form a prefix of it).
+    // Prologue.  bf16: copies the page window, Q, K(0), V(0) .. K(kS/2 - 1), V(kS/2 - 1) without
+    // a wait between them, Q (this wave's 32 columns, laid out as a sub-block of K) in the upper
+    // half of the K and V rings; once K(0) and Q have arrived and every wave has read its Q,
+    // the rest of the first kS - 1 tiles and K(kS - 1) go over it.  Sub-block 0 sets the
+    // reference to its own max (a lane with no visible key there has none in the group's range,
+    // as its visible keys form a prefix of it).
+    // A workgroup's fixed cost is latency: this order, the item, status, item count and page ids
+    // loaded together, and 16-byte output stores took a launch with few tiles (P = 256, C = 128,
+    // 8q/2kv, 256 columns) from 16.0 to 13.1 us, a first 512-token chunk (32q/8kv) from 19.7 to
+    // 16.7 us and the fused 8K-prefix layer from 76.9 to 74.6 us, against Q loaded into registers
+    // and waited for before the first copy.
     if constexpr (!kFp8) {
+      constexpr int kEarly = kS / 2;    // tiles copied before Q has been read
+      fetch_window(0, 1);
+      if (ntiles > 64 - kS - 2) fetch_window(64, 0);
+      // column c of this wave (tile column 32 cw + c): its Q row's chunk k at chunk k ^ (c & 15)
+      // of row c; columns past the item's tokens read as zeros
+      const int qofs = (cw < kColWaves / 2 ? kKBase + (kEarly + cw / 2) * kTileBytes
+                                           : kVBase + (kEarly + (cw - kColWaves / 2) / 2) * kTileBytes) +
+                       (cw & 1) * kSubBytes;
+      {
+        const int t0 = div_g(32 * cw);
+        const int nt = min(i1 - i0 - t0, 33);   // at most 32 tokens and a part of one more
+        const i32x4 qrs = sgpr_rsrc(q + ((int64_t)(row0 + i0 + t0) * hq + g * G) * kHeadDim,
+                                    nt > 0 ? ((nt - 1) * hq + G) * kRowBytes : 0);
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem + grp_base + qofs;
 #pragma unroll
-      for (int j = 0; j < kS - 1; ++j) {
+        for (int d = 0; d < 8; ++d) {
+          const int c = 4 * d + (lane >> 4), t = div_g(32 * cw + c), h = 32 * cw + c - t * G;
+          const uint32_t voff = (uint32_t)(((t - t0) * hq + h) * kRowBytes + (((lane & 15) ^ (c & 15)) << 4));
+          lds_dma_b128(qrs, voff, __builtin_amdgcn_readfirstlane(lds0 + d * 1024));
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kEarly; ++j) {
+        dma_rows(true, pg[j], lo + j * kKvTile, kKBase + j * kTileBytes);
+        dma_rows(false, pg[j], lo + j * kKvTile, kVBase + j * kTileBytes);
+      }
+      wait_vmcnt<2 * kEarly * kDma>();   // the windows and Q
+      __asm__ volatile("" ::: "memory");
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(smem + qofs + ka[ks]);
+      pg_win = s_pages[wave][1][lane];
+      wait_vmcnt<(2 * kEarly - 1) * kDma>();   // K(0)
+      wait_lgkmcnt0();                         // Q is in registers
+      __builtin_amdgcn_s_barrier();
+      append_rows();
+#pragma unroll
+      for (int j = kEarly; j < kS - 1; ++j) {
         dma_rows(true, pg[j], lo + j * kKvTile, kKBase + j * kTileBytes);
         dma_rows(false, pg[j], lo + j * kKvTile, kVBase + j * kTileBytes);
       }
       dma_rows(true, pg[kS - 1], lo + (kS - 1) * kKvTile, kKBase + (kS - 1) * kTileBytes);
       pg_klast = pg[kS - 1];
       pg_knext = pg[kS];
-      wait_vmcnt<(2 * kS - 2) * kDma>();   // K(0), the first of these copies
     } else {
-      const int32_t pg0 = pg[0], pg1 = pg[1];
-      f8_load(kst, kpb, pg0, lo, kvo);
-      f8_load(vst, vpb, pg0, lo, vvo);
+      f8_load(kst, kpb, pg[0], lo, kvo);
+      f8_load(vst, vpb, pg[0], lo, vvo);
+      fetch_window(0, 1);
+      if (ntiles > 64 - kS - 2) fetch_window(64, 0);
       f8_store(kst, kKBase, true);
       f8_store(vst, kVBase, false);
-      f8_load(kst, kpb, pg1, lo + kKvTile, kvo);
+      f8_load(kst, kpb, pg[1], lo + kKvTile, kvo);
       f8_store(kst, kKBase + kTileBytes, true);
-      pg_klast = pg1;
+      pg_klast = pg[1];
       pg_knext = pg[2];
+      // the windows, and every load: one still pending in the compiler's count on some path
+      // would make it wait for all of them in each step of the loop
+      wait_vmcnt<0>();
+      __asm__ volatile("" ::: "memory");
+      pg_win = s_pages[wave][1][lane];
       wait_lgkmcnt0();
+      __builtin_amdgcn_s_barrier();
     }
-    __builtin_amdgcn_s_barrier();
 
     sp = qk(kKBase);
     mask(sp, lo);
@@ -760,6 +841,8 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
     }
     probs(sp, pa, lsum_p);
     sc = qk(kKBase + kSubBytes);
+  } else {
+    append_rows();
   }
 
   int t = 0;
@@ -851,7 +934,7 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   // token are adjacent) with device-scope (sc1) stores, which write through the L2: no
   // dirty partial lines are left for the write-back at the end of the launch.  The row sum
   // and max follow with the same policy.
-  float* const acc = pv.partials + it.part_off;
+  float* const acc = partials + it.part_off;
   const int64_t acc_bytes = (int64_t)ns * C * hq * (kHeadDim + 4) * 4;
   if (kHalves == 1 && RingT::kBytes >= kColWaves * 32 * kHeadDim * 4 && ns > 1 && acc_bytes <= 0x7fffffff) {
     constexpr int kSc1 = 16;   // cache policy: device scope
@@ -868,18 +951,15 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
     __builtin_amdgcn_s_barrier();
     const auto prs = make_rsrc(acc, (int32_t)acc_bytes);
     const int ncols = min(tq * G, (i1 - i0) * G);   // the valid columns of this tile
-    // row of column c: (s C + i0 + c / G) hq + g G + c % G = rbase + c + (c / G)(hq - G);
-    // c / G = (c ginv) >> 24 exactly for c < 256 and G < 2^16
+    // row of column c: (s C + i0 + c / G) hq + g G + c % G = rbase + c + (c / G)(hq - G)
     const int64_t rbase = ((int64_t)it.s * C + i0) * hq + g * G;
-    const uint32_t ginv = ((1u << 24) + (uint32_t)G - 1) / (uint32_t)G;
-    constexpr int kThreads = kColWaves * 64;
 #pragma unroll
     for (int u0 = 0; u0 < 32 * kColWaves * 32; u0 += kThreads) {
       const int u = u0 + (int)threadIdx.x;
       const int c = u >> 5, k = u & 31;   // column, 16-byte chunk
       if (c < ncols) {
         const f32x4 x = *reinterpret_cast<const f32x4*>(xs + (c * 32 + (k ^ (c & 15))) * 4);
-        const int64_t pr = rbase + c + (int64_t)(((uint32_t)c * ginv) >> 24) * (hq - G);
+        const int64_t pr = rbase + c + (int64_t)div_g(c) * (hq - G);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), prs, (uint32_t)(pr * 512 + 16 * k), 0,
                                                kSc1);
       }
@@ -895,14 +975,19 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   if (!valid) return;
   if (ns == 1) {
     const float inv = v_mul / l_fin;
-    uint16_t* orow = out + ((int64_t)(row0 + tok) * hq + hq_col) * 128 + 4 * half;
+    // the lane pair holds dims 8 j + {0..3} and 8 j + {4..7} of a block: exchanged so that the
+    // lower lane stores the eight dims of an even j, the upper one those of the next j
+    uint16_t* orow = out + ((int64_t)(row0 + tok) * hq + hq_col) * 128 + 8 * half;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const u32x2 w = {pack_bf16x2(o[db][4 * j] * inv, o[db][4 * j + 1] * inv),
-                         pack_bf16x2(o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv)};
-        *reinterpret_cast<u32x2*>(orow + 32 * db + 8 * j) = w;
+      for (int j = 0; j < 4; j += 2) {
+        u32x2 w[2];   // [first, second word of the lane's four dims of j and of j + 1]
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          w[e] = swap_halves(pack_bf16x2(o[db][4 * j + 2 * e] * inv, o[db][4 * j + 2 * e + 1] * inv),
+                             pack_bf16x2(o[db][4 * j + 4 + 2 * e] * inv, o[db][4 * j + 5 + 2 * e] * inv));
+        *reinterpret_cast<u32x4*>(orow + 32 * db + 8 * j) = u32x4{w[0][0], w[1][0], w[0][1], w[1][1]};
       }
     if (lse != nullptr && half == 0) lse[(int64_t)(row0 + tok) * hq + hq_col] = (m_fin + __log2f(l_fin)) * kLn2;
     return;
@@ -995,10 +1080,14 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(uint16_t* __restrict_
 
 template <bool kFp8, int kColWaves, int kHalves, bool kFused, bool kQ8 = false>
 void launch_main_variant(const AttnLaunch& a, hipStream_t stream) {
+  const PlanPtrs pv = plan_ptrs(a.workspace, a.dims);
+  const int32_t g = a.hq / a.kv.hkv;
+  const uint32_t ginv = ((1u << 24) + (uint32_t)g - 1) / (uint32_t)g;
   attn_main_kernel<kFp8, kColWaves, kHalves, kFused, kQ8><<<(unsigned)a.dims.num_items, kColWaves * kHalves * 64, 0, stream>>>(
-      static_cast<const uint16_t*>(a.q), static_cast<uint16_t*>(a.out), a.lse, a.kv.kpool, a.kv.vpool,
-      a.kv.kscale, a.kv.vscale, a.kv.block_tables, a.kv.max_pages, a.hq, a.kv.hkv, a.softmax_scale * kLog2e,
-      plan_ptrs(a.workspace, a.dims), a.group_by_xcd ? 1 : 0, static_cast<const uint16_t*>(a.knew),
+      pv.items, pv.hdr, a.group_by_xcd ? (int32_t)a.dims.num_items : 0, a.kv.max_pages, a.kv.block_tables,
+      static_cast<const uint16_t*>(a.q), a.hq, g, ginv, tile_tokens(g, 32 * kColWaves),
+      static_cast<uint16_t*>(a.out), a.lse, a.kv.kpool, a.kv.vpool, a.kv.kscale, a.kv.vscale, a.kv.hkv,
+      a.softmax_scale * kLog2e, pv.partials, static_cast<const uint16_t*>(a.knew),
       static_cast<const uint16_t*>(a.vnew), a.total_rows);
 }
 

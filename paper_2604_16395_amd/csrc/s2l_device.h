@@ -74,6 +74,13 @@ __device__ inline float sum_with_partner(float x) {
   return x;
 }
 
+// Two words of a lane pair (l, l + 32) exchanged crosswise: the lower lane returns (its a, the
+// upper lane's a), the upper lane (the lower lane's b, its b).
+__device__ inline u32x2 swap_halves(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return u32x2{r[0], r[1]};
+}
+
 // Outputs of a launch whose device plan did not fit the host's sizing (its status word is
 // not 0: the device length arrays disagree with the host copies, and nothing was planned).
 // Every workgroup writes NaN over its share of the `rows` output rows the host sized the

@@ -1,0 +1,44 @@
+"""GPU: sizes at the edges of the kernels' dispatch rules and of their inner blocking, against
+the fp64 oracle and, where two routes must agree bit for bit, against each other."""
+import pytest
+import torch
+
+import paper_2604_16395_amd as s2l
+import workloads
+from tests.gpu_util import DEV, SCALE, Setup, assert_attention_close, to_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(case, opts, fused):
+    s = Setup(case)
+    T, hq, hkv = case.total_tokens, case.num_q_heads, case.num_kv_heads
+    ws = torch.empty(s2l.s2l_attn_workspace_bytes(s.batch, hq, hkv, opts), dtype=torch.uint8, device=DEV)
+    s.plan = plan = s2l.s2l_attn_plan(s.batch, hq, hkv, ws, opts)
+    out = torch.full((T, hq, 128), float("nan"), dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((T, hq), float("nan"), dtype=torch.float32, device=DEV)
+    if fused:
+        assert s2l.s2l_append_chunk_prefill_attn(s.cache, s.batch, to_bf16(s.k_new), to_bf16(s.v_new), s.q, hq, SCALE,
+                                                 out, lse, plan, ws)
+    else:
+        s.append()
+        s2l.s2l_chunk_prefill_attn(s.cache, s.batch, s.q, hq, SCALE, out, lse, plan, ws)
+    torch.cuda.synchronize()
+    return s, out, lse
+
+
+@pytest.mark.parametrize("layout", [(256, 1), (128, 1), (128, 2)])
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (7, 1), (96, 1)])
+def test_fused_append_of_wide_tiles_and_odd_groups(hq, hkv, layout):
+    """Tiles of up to 256 tokens (one head per kv head: more rows to append than a workgroup holds
+    in flight), and group sizes that do not divide the tile (its last columns belong to no token),
+    with the last tile one token long."""
+    tq = layout[0] // (hq // hkv)
+    case = workloads.make_case("append", [0, 64, 1024], [tq + 1, tq, 1], hq, hkv, seed=51)
+    opts = s2l.plan_opts(tile_cols=layout[0], key_halves=layout[1])
+    a, oa, la = _call(case, opts, True)
+    b, ob, lb = _call(case, opts, False)
+    for x, y in ((a.cache.k_pages, b.cache.k_pages), (a.cache.v_pages, b.cache.v_pages), (oa, ob)):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+    assert torch.equal(la, lb)
+    assert_attention_close(case, oa, la, b.oracle(), what=f"G={hq // hkv} {layout}")
