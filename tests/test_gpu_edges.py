@@ -42,3 +42,20 @@ def test_fused_append_of_wide_tiles_and_odd_groups(hq, hkv, layout):
         assert torch.equal(x.view(torch.int16), y.view(torch.int16))
     assert torch.equal(la, lb)
     assert_attention_close(case, oa, la, b.oracle(), what=f"G={hq // hkv} {layout}")
+
+
+@pytest.mark.parametrize("pieces", [2, 4, 5, 8, 9, 16, 31, 33, 64])
+def test_merge_of_few_and_many_pieces(pieces):
+    """The split merge on both sides of its limits (four pieces: loaded by every lane; eight in
+    flight; 32 a half wave), for three heads (a half wave without a row), with requests that are
+    not split and a request index past the first 64 among the rows it has to find."""
+    P = [64 * pieces - 3] + [0] * 70 + [64 * pieces - 40]
+    C = [3] + [1] * 70 + [5]
+    case = workloads.make_case("merge", P, C, 3, 1, seed=52)
+    s = Setup(case)
+    s.append()
+    for tc in (16, 128):
+        opts = s2l.plan_opts(tile_cols=tc, target_items=1 << 20, min_split_keys=64, max_splits=pieces)
+        out, lse = s.attention(opts)
+        assert s.plan.num_split_reqs == 2
+        assert_attention_close(case, out, lse, s.oracle(), what=f"{pieces} pieces, {tc} columns")
