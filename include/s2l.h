@@ -109,8 +109,10 @@ typedef struct s2l_batch {
 typedef struct s2l_plan_opts {
   int32_t target_items;    /* work items wanted before prefixes are split; 0 = the number   */
                            /* of workgroups the GPU holds at once (CUs x 1 or x 2)          */
-  int32_t min_split_keys;  /* smallest key range of a split piece; 0 = 512 (rounded to 64) */
-  int32_t max_splits;      /* most pieces per request; 0 = 16 (at most 64)                  */
+  int32_t min_split_keys;  /* smallest key range of a split piece; 0 = 512, or 256 for      */
+                           /* 16-column tiles (rounded to 64)                               */
+  int32_t max_splits;      /* most pieces per request; 0 = 16, or 32 for 16-column tiles    */
+                           /* (at most 64)                                                  */
   int32_t tile_cols;       /* query columns (tokens x heads of one kv head) per work item:  */
                            /* 128 or 256; 0 = automatic: 256 unless such tiles would be     */
                            /* less than half full on average (mostly decode-like rows)      */
@@ -240,7 +242,8 @@ s2l_status s2l_attn_workspace_bytes(const s2l_batch* batch, int32_t num_q_heads,
  * tiles, each request's key range 0 .. P_r + i_end is split into up to max_splits pieces of
  * >= min_split_keys keys (never more items than target_items in total), so that long
  * prefixes spread over more workgroups (their partial results are merged by
- * s2l_split_reduce).  With key_halves = 2 a work item's own range is
+ * s2l_split_reduce); with target_items 0, 16-column tiles are also cut so that no piece of a
+ * batch of few tiles is above 4096 keys.  With key_halves = 2 a work item's own range is
  * further halved between two wave groups of its workgroup, merged in LDS.
  *   workspace : device, ws_bytes >= s2l_attn_workspace_bytes(...).
  *   info      : HOST out, describes the plan; pass it to the attention calls.

@@ -53,6 +53,7 @@ s2l_status hip_fail(const char* what, hipError_t e) {
 
 struct Resolved {
   int32_t target_items, min_split_keys, max_splits, tile_cols, key_halves;
+  int32_t max_piece_keys;   // 0 = none: pieces are only as short as target_items asks for
 };
 
 // Automatic tile width: 16-column decode tiles when every request fits one (C * G <= 16:
@@ -74,8 +75,10 @@ int32_t auto_tile_cols(int32_t R, const int32_t* C, int32_t hq, int32_t hkv) {
   return 2 * used >= alloc ? s2l::kMaxTileCols : s2l::kMinTileCols;
 }
 
+// `frugal` keeps to the rules that need the least workspace: pieces only to fill the GPU, at most 16
+// a request, none for decode tiles below 512 keys.
 s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, int32_t R, const int32_t* C,
-                        int32_t hq, int32_t hkv, Resolved* r) {
+                        int32_t hq, int32_t hkv, Resolved* r, bool frugal = false) {
   int32_t t = o ? o->target_items : 0, m = o ? o->min_split_keys : 0, x = o ? o->max_splits : 0;
   int32_t tc = o ? o->tile_cols : 0, kh = o ? o->key_halves : 0;
   if (t < 0 || m < 0 || x < 0) return fail(S2L_EINVAL, "plan opts must be >= 0");
@@ -100,8 +103,13 @@ s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, 
     t = s2l::items_per_cu(r->tile_cols, r->key_halves) * num_cus;
   }
   r->target_items = t;
-  r->min_split_keys = (int32_t)s2l::align_up(m > 0 ? m : s2l::kDefaultMinSplitKeys, s2l::kKvTile);
-  r->max_splits = x > 0 ? (x < s2l::kMaxSplitsCap ? x : s2l::kMaxSplitsCap) : s2l::kDefaultMaxSplits;
+  const bool decode = r->tile_cols == s2l::kDecodeTileCols && !frugal;
+  const int32_t min_keys = decode ? s2l::kDecodeMinSplitKeys : s2l::kDefaultMinSplitKeys;
+  const int32_t max_splits = decode ? s2l::kDecodeMaxSplits : s2l::kDefaultMaxSplits;
+  r->min_split_keys = (int32_t)s2l::align_up(m > 0 ? m : min_keys, s2l::kKvTile);
+  r->max_splits = x > 0 ? (x < s2l::kMaxSplitsCap ? x : s2l::kMaxSplitsCap) : max_splits;
+  r->max_piece_keys = decode && (!o || o->target_items == 0)
+                          ? std::max<int32_t>(s2l::kDecodeMaxPieceKeys, r->min_split_keys) : 0;
   return S2L_OK;
 }
 
@@ -182,8 +190,8 @@ int64_t items_for(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, in
   return n;
 }
 
-// Piece length of the batch: 0 (no split) when the batch already has at least target_items
-// query tiles; else the shortest multiple of 64 keys (at least min_split_keys) for which
+// Piece length of the batch: 0 (no split) when the batch already has at least target_items query
+// tiles; else, and never above max_piece_keys where that is set, the shortest multiple of 64 keys (at least min_split_keys) for which
 // cutting every request into ceil((P + C) / length) pieces (at most max_splits) gives no
 // more than target_items items, so that one round of workgroups covers the launch and the
 // longest item is as short as that allows.  Item counts fall as the length grows, so the
@@ -204,7 +212,8 @@ int32_t choose_split_keys(int32_t R, const int32_t* P, const int32_t* C, int32_t
     if (items_for(R, P, C, hkv, tq, (int32_t)(mid * s2l::kKvTile), o.max_splits) <= o.target_items) hi = mid;
     else lo = mid;
   }
-  return (int32_t)(hi * s2l::kKvTile);
+  const int32_t keys = (int32_t)(hi * s2l::kKvTile);
+  return o.max_piece_keys > 0 ? std::min(keys, o.max_piece_keys) : keys;
 }
 
 // Binned item order (plan_rules.h): requests ranked as the device plan ranks them, their
@@ -370,6 +379,7 @@ s2l_status attn_launch(const s2l_kv_cache* cache, const s2l_batch* batch, const 
   a.dims = plan_dims(plan);
   a.tile_cols = plan->tile_cols;
   a.key_halves = plan->key_halves;
+  a.uniform = (plan->flags & S2L_PLAN_UNIFORM) != 0;
   a.group_by_xcd = (plan->flags & (S2L_PLAN_UNIFORM | S2L_PLAN_BINNED)) != 0;
   a.knew = k_new;
   a.vnew = v_new;
@@ -378,6 +388,44 @@ s2l_status attn_launch(const s2l_kv_cache* cache, const s2l_batch* batch, const 
   (void)hipGetLastError();
   hipError_t e = s2l::launch_attn_main(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail("attn_main launch", e);
+  return ok();
+}
+
+// The device plan of a checked batch with resolved options.
+s2l_status plan_resolved(const s2l_batch* batch, int32_t hq, int32_t hkv, const Resolved& o, void* workspace,
+                         size_t ws_bytes, s2l_plan_info* info, void* stream) {
+  s2l_plan_info pi;
+  host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, hq, hkv, o, &pi, nullptr, 0);
+  if (!workspace) return fail(S2L_EWORKSPACE, "workspace is NULL");
+  if ((int64_t)ws_bytes < pi.workspace_bytes)
+    return fail(S2L_EWORKSPACE, "workspace %zu bytes < %lld needed", ws_bytes, (long long)pi.workspace_bytes);
+  if (batch->num_reqs == 0 && !batch->cu_chunk) {
+    *info = pi;  // empty batch: nothing for the kernels to read
+    return ok();
+  }
+  s2l::PlanLaunch a;
+  a.prefix_lens = batch->prefix_lens;
+  a.chunk_lens = batch->chunk_lens;
+  a.cu_chunk = batch->cu_chunk;
+  a.num_reqs = batch->num_reqs;
+  a.hq = hq;
+  a.hkv = hkv;
+  a.split_keys = pi.split_keys;
+  a.max_splits = o.max_splits;
+  a.tile_cols = o.tile_cols;
+  a.binned = (pi.flags & S2L_PLAN_BINNED) != 0;
+  if (a.binned) {
+    int32_t len;
+    const int32_t tq = s2l::tile_tokens(hq / hkv, o.tile_cols);
+    bin_groups(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, hkv, tq, pi.split_keys, o.max_splits,
+               a.group_bin, &len);
+  }
+  a.ws_bytes = (int64_t)ws_bytes;
+  a.workspace = workspace;
+  (void)hipGetLastError();
+  hipError_t e = s2l::launch_attn_plan(a, plan_dims(&pi), static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return hip_fail("attn_plan launch", e);
+  *info = pi;
   return ok();
 }
 
@@ -546,40 +594,7 @@ s2l_status s2l_attn_plan(const s2l_batch* batch, int32_t num_q_heads, int32_t nu
   if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
       S2L_OK)
     return st;
-  s2l_plan_info pi;
-  host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, num_kv_heads, o, &pi,
-            nullptr, 0);
-  if (!workspace) return fail(S2L_EWORKSPACE, "workspace is NULL");
-  if ((int64_t)ws_bytes < pi.workspace_bytes)
-    return fail(S2L_EWORKSPACE, "workspace %zu bytes < %lld needed", ws_bytes, (long long)pi.workspace_bytes);
-  if (batch->num_reqs == 0 && !batch->cu_chunk) {
-    *info = pi;  // empty batch: nothing for the kernels to read
-    return ok();
-  }
-  s2l::PlanLaunch a;
-  a.prefix_lens = batch->prefix_lens;
-  a.chunk_lens = batch->chunk_lens;
-  a.cu_chunk = batch->cu_chunk;
-  a.num_reqs = batch->num_reqs;
-  a.hq = num_q_heads;
-  a.hkv = num_kv_heads;
-  a.split_keys = pi.split_keys;
-  a.max_splits = o.max_splits;
-  a.tile_cols = o.tile_cols;
-  a.binned = (pi.flags & S2L_PLAN_BINNED) != 0;
-  if (a.binned) {
-    int32_t len;
-    const int32_t tq = s2l::tile_tokens(num_q_heads / num_kv_heads, o.tile_cols);
-    bin_groups(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_kv_heads, tq, pi.split_keys,
-               o.max_splits, a.group_bin, &len);
-  }
-  a.ws_bytes = (int64_t)ws_bytes;
-  a.workspace = workspace;
-  (void)hipGetLastError();
-  hipError_t e = s2l::launch_attn_plan(a, plan_dims(&pi), static_cast<hipStream_t>(stream));
-  if (e != hipSuccess) return hip_fail("attn_plan launch", e);
-  *info = pi;
-  return ok();
+  return plan_resolved(batch, num_q_heads, num_kv_heads, o, workspace, ws_bytes, info, stream);
 }
 
 s2l_status s2l_attn_main(const s2l_kv_cache* cache, const s2l_batch* batch, const void* q, int32_t num_q_heads,
@@ -670,13 +685,17 @@ s2l_status s2l_chunk_prefill_attn_noalloc(const s2l_kv_cache* cache, const s2l_b
   if (!(softmax_scale > 0.0f) || !std::isfinite(softmax_scale))
     return fail(S2L_EINVAL, "softmax_scale must be finite and > 0");
   if (T > 0 && (!q || !out)) return fail(S2L_EINVAL, "q/out is NULL");
+  // a batch whose plan does not fit the scratch is planned again with the least workspace
   Resolved o;
-  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads,
-                         &o)) != S2L_OK)
-    return st;
   s2l_plan_info pi;
-  host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads, o,
-            &pi, nullptr, 0);
+  for (const bool frugal : {false, true}) {
+    if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads,
+                           &o, frugal)) != S2L_OK)
+      return st;
+    host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads, o,
+              &pi, nullptr, 0);
+    if (pi.workspace_bytes <= (int64_t)s2l::kNoAllocScratchBytes) break;
+  }
   if (pi.workspace_bytes > (int64_t)s2l::kNoAllocScratchBytes)
     return fail(S2L_EWORKSPACE,
                 "this batch needs %lld bytes of workspace, more than the %zu bytes of scratch the allocation-free "
@@ -686,8 +705,8 @@ s2l_status s2l_chunk_prefill_attn_noalloc(const s2l_kv_cache* cache, const s2l_b
   hipError_t e = s2l::noalloc_scratch(&ws);
   if (e != hipSuccess) return hip_fail("taking the scratch array's device address", e);
   s2l_plan_info info;
-  if ((st = s2l_attn_plan(batch, num_q_heads, cache->num_kv_heads, opts, ws, s2l::kNoAllocScratchBytes, &info,
-                          stream)) != S2L_OK)
+  if ((st = plan_resolved(batch, num_q_heads, cache->num_kv_heads, o, ws, s2l::kNoAllocScratchBytes, &info, stream)) !=
+      S2L_OK)
     return st;
   if ((st = s2l_chunk_prefill_attn(cache, batch, q, num_q_heads, softmax_scale, out, lse, &info, ws,
                                    s2l::kNoAllocScratchBytes, stream)) != S2L_OK)

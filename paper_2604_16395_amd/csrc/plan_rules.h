@@ -28,13 +28,24 @@ constexpr int kKvTile = 64;         // keys per LDS tile
 constexpr int kMaxSplitsCap = 64;
 constexpr int kDefaultMinSplitKeys = 512;
 constexpr int kDefaultMaxSplits = 16;
+// Decode tiles, by default.  Pieces down to 256 keys (two 32-key tiles a wave): one row over 2047
+// keys (32q/8kv, bf16) takes 12.7 us a layer with 512-key pieces, 10.9 with 256, 11.6 with 128,
+// where the merge costs more than the shorter pieces save.  At most 32 pieces: one row over
+// 32768 keys takes 38.3 us with 16, 35.7 with 32, 41.6 with 64.  A batch that is split at all is
+// split into pieces of at most 4096 keys, as the longest would end alone (24 requests up to 16K
+// keys, 64q/8kv, fp8: 88.2 us with pieces up to 9984 keys, 82.3 up to 3840, 85.3 up to 1664).
+constexpr int kDecodeMinSplitKeys = 256;
+constexpr int kDecodeMaxSplits = 32;
+constexpr int kDecodeMaxPieceKeys = 4096;
 constexpr int32_t kPlanMagic = 0x53324c50;  // "S2LP"
 
 // Work items resident per CU: a 128-column item is a 4-wave workgroup with a two-stage
 // K/V ring (64 KiB of LDS), two per CU, or with two key-range groups an 8-wave workgroup
 // with two such rings (128 KiB), one per CU; a 256-column item is an 8-wave workgroup with
-// a four-stage ring (128 KiB), one per CU; a 16-column item is a 4-wave workgroup whose
-// waves hold two tiles of K and V in registers each (up to 512 registers), one per CU.
+// a four-stage ring (128 KiB), one per CU; for a 16-column item (a 4-wave workgroup, of which two
+// could share a CU) launches are planned for one each: what a CU reads is bound by the memory,
+// not by its waves, and a launch a little over one round of workgroups doubles some CUs up (8
+// requests of up to 4096 keys, 32q/8kv: 256 items 21.1 us a layer, 312 items 24.2 us).
 S2L_HD inline int32_t items_per_cu(int32_t tile_cols, int32_t key_halves) {
   return tile_cols == kMaxTileCols || tile_cols == kDecodeTileCols || key_halves == 2 ? 1 : 2;
 }

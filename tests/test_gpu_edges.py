@@ -59,3 +59,46 @@ def test_merge_of_few_and_many_pieces(pieces):
         out, lse = s.attention(opts)
         assert s.plan.num_split_reqs == 2
         assert_attention_close(case, out, lse, s.oracle(), what=f"{pieces} pieces, {tc} columns")
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (12, 4), (64, 8)])
+def test_decode_tiles_at_their_edges(hq, hkv, kv_dtype):
+    """One-token rows whose key counts lie around the tiles of one wave (32 keys bf16, 64 fp8), of
+    the four waves, and the default piece length, unsplit, in the planner's pieces and in 64-key
+    pieces (waves without a tile)."""
+    P = [n - 1 + d for n in (32, 64, 128, 256, 512) for d in (-1, 0, 1)]
+    case = workloads.make_case("dec_edges", P, [1] * len(P), hq, hkv, seed=53, kv_dtype=kv_dtype)
+    s = Setup(case)
+    s.append()
+    for opts in (s2l.plan_opts(target_items=1), None, s2l.plan_opts(target_items=1 << 20, min_split_keys=64)):
+        out, lse = s.attention(opts)
+        assert s.plan.tile_cols == 16
+        assert_attention_close(case, out, lse, s.oracle(), what=f"{kv_dtype} G={hq // hkv}")
+
+
+def test_allocation_free_call_keeps_to_its_scratch():
+    """Decode rows whose default plan (pieces of up to 4096 keys) needs more than the library's
+    scratch: the allocation-free call plans them unsplit instead of refusing them."""
+    R, P, hq, hkv, pool = 255, 131071, 16, 1, 64
+    gen = torch.Generator(device=DEV).manual_seed(54)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)
+    cache = s2l.PagedKVCache(rnd(pool, hkv, 16, 128), rnd(pool, hkv, 16, 128))
+    tables = torch.randint(0, pool, (R, P // 16 + 1), generator=torch.Generator().manual_seed(54), dtype=torch.int32)
+    batch = s2l.Batch([P] * R, [1] * R, tables.numpy())
+    assert s2l.s2l_attn_workspace_bytes(batch, hq, hkv) > s2l.NOALLOC_SCRATCH_BYTES
+    q, out, ref = rnd(R, hq, 128), torch.empty_like(rnd(R, hq, 128)), torch.empty_like(rnd(R, hq, 128))
+    info = s2l.s2l_chunk_prefill_attn_noalloc(cache, batch, q, hq, SCALE, out, None)
+    assert info.num_split_reqs == 0
+    ws = torch.empty(s2l.s2l_attn_workspace_bytes(batch, hq, hkv), dtype=torch.uint8, device=DEV)
+    plan = s2l.s2l_attn_plan(batch, hq, hkv, ws)
+    assert plan.num_split_reqs == R
+    s2l.s2l_chunk_prefill_attn(cache, batch, q, hq, SCALE, ref, None, plan, ws)
+    # Each result is sum(p v) / sum(p) over probabilities rounded to bf16 (2^-9 each, in the sum and
+    # in its divisor: 2^-8 A, A = sum(p |v|) / sum(p)), rounded to bf16 (2^-9 |O|).  The two differ by
+    # at most twice that; A comes from the same call over |V|, itself good to 2^-6.
+    a = torch.empty_like(ref)
+    s2l.s2l_chunk_prefill_attn(s2l.PagedKVCache(cache.k_pages, cache.v_pages.abs()), batch, q, hq, SCALE, a, None,
+                               plan, ws)
+    bound = 2.0 ** -7 * (1 + 2.0 ** -6) * a.float() + 2.0 ** -8 * ref.float().abs()
+    assert torch.all((out.float() - ref.float()).abs() <= bound)
