@@ -68,9 +68,9 @@ struct PlanHeader {           // first 256 bytes of the workspace
 struct ItemRec {
   int32_t r, g, i0, i1;       // request, kv head, chunk tokens [i0, i1)
   int32_t lo, hi, s, ns;      // key range [lo, hi), piece s of ns
-  int32_t p, c, row0, tile;   // P_r, C_r, first row of the request, query-tile index
+  int32_t p, c, row0, pad0;   // P_r, C_r, first row of the request
   int64_t part_off;           // floats: start of the request's partials
-  int32_t pad0, pad1;
+  int32_t pad1, pad2;
 };
 static_assert(sizeof(ItemRec) == 64, "ItemRec is one 64-byte scalar load");
 

@@ -1,5 +1,6 @@
 """GPU: sizes at the edges of the kernels' dispatch rules and of their inner blocking, against
 the fp64 oracle and, where two routes must agree bit for bit, against each other."""
+import numpy as np
 import pytest
 import torch
 
@@ -102,3 +103,35 @@ def test_allocation_free_call_keeps_to_its_scratch():
                                plan, ws)
     bound = 2.0 ** -7 * (1 + 2.0 ** -6) * a.float() + 2.0 ** -8 * ref.float().abs()
     assert torch.all((out.float() - ref.float()).abs() <= bound)
+
+
+@pytest.mark.parametrize("R,hkv", [(1, 1), (1, 8), (2, 1), (3, 5), (63, 2), (65, 1), (256, 4), (257, 1), (1024, 1), (1025, 1)])
+def test_device_plan_equals_the_host_plan(R, hkv):
+    """The item records the device wrote (in any order, padding aside) are the host planner's, at
+    the request counts where the plan kernel changes its way: one, a wave, the ranked and binned
+    limit (256), requests kept in LDS (1024)."""
+    rng = np.random.default_rng(55 + R)
+    P, C = rng.integers(0, 900, R), rng.integers(0, 90, R)
+    C[0] = 5
+    hq = 4 * hkv
+    batch = s2l.Batch(P, C, np.zeros((R, 64), np.int32))
+    for opts in (None, s2l.plan_opts(target_items=1 << 20, min_split_keys=64)):
+        ws = torch.zeros(s2l.s2l_attn_workspace_bytes(batch, hq, hkv, opts), dtype=torch.uint8, device=DEV)
+        plan = s2l.s2l_attn_plan(batch, hq, hkv, ws, opts)
+        assert s2l.plan_status(ws).item() == 0
+        _, items = s2l.s2l_plan_host(P, C, hq, hkv, opts, num_cus=torch.cuda.get_device_properties(0).multi_processor_count,
+                                     with_items=True)
+        assert len(items) == plan.num_items
+        # records: 64 bytes each after the header and the request arrays (item_off, ns, c, cu, part_off)
+        off = 256 + 4 * (4 * R + 2)
+        off = (-(-off // 8) * 8 + 8 * R + 63) // 64 * 64
+        rec = ws.cpu().numpy()[off:off + 64 * plan.num_items].view(np.int32).reshape(-1, 16)
+        cu = np.concatenate([[0], np.cumsum(C)])
+        real = rec[rec[:, 0] >= 0]
+        got = sorted(map(tuple, real[:, :8].tolist()))
+        # host rows: request, kv head, i0, i1, lo, hi, piece, pieces: the record's own order
+        assert got == sorted(map(tuple, items[items[:, 0] >= 0].tolist()))
+        r = real[:, 0]
+        assert np.array_equal(real[:, 8], P[r]) and np.array_equal(real[:, 9], C[r]) and np.array_equal(real[:, 10], cu[r])
+        pad = rec[rec[:, 0] < 0]
+        assert len(pad) == (items[:, 0] < 0).sum() and np.all(pad[:, 0] == -1)
