@@ -54,7 +54,43 @@ s2l_status hip_fail(const char* what, hipError_t e) {
 struct Resolved {
   int32_t target_items, min_split_keys, max_splits, tile_cols, key_halves;
   int32_t max_piece_keys;   // 0 = none: pieces are only as short as target_items asks for
+  bool unsplit;             // key ranges are left whole
 };
+
+// Items of the batch when every request is cut into pieces of at most split_keys keys.
+int64_t items_for(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, int32_t tq, int32_t split_keys,
+                  int32_t max_splits) {
+  int64_t n = 0;
+  for (int32_t r = 0; r < R; ++r)
+    n += (int64_t)hkv * s2l::num_qtiles(C[r], tq) * s2l::req_splits(P[r], C[r], split_keys, max_splits);
+  return n;
+}
+
+// Piece length of the batch: 0 (no split) when the batch already has at least target_items query
+// tiles; else, and never above max_piece_keys where that is set, the shortest multiple of 64 keys (at least min_split_keys) for which
+// cutting every request into ceil((P + C) / length) pieces (at most max_splits) gives no
+// more than target_items items, so that one round of workgroups covers the launch and the
+// longest item is as short as that allows.  Item counts fall as the length grows, so the
+// shortest such length is found by bisection.
+int32_t choose_split_keys(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, int32_t tq,
+                          const Resolved& o) {
+  int64_t tiles = 0, longest = 0;
+  for (int32_t r = 0; r < R; ++r) {
+    tiles += (int64_t)hkv * s2l::num_qtiles(C[r], tq);
+    if (C[r] > 0 && (int64_t)P[r] + C[r] > longest) longest = (int64_t)P[r] + C[r];
+  }
+  if (tiles == 0 || tiles >= o.target_items || o.unsplit) return 0;
+  const int64_t lo_keys = s2l::align_up(o.min_split_keys, s2l::kKvTile);
+  int64_t lo = lo_keys / s2l::kKvTile, hi = std::max(lo, s2l::ceil_div64(longest, s2l::kKvTile));
+  if (items_for(R, P, C, hkv, tq, (int32_t)(lo * s2l::kKvTile), o.max_splits) <= o.target_items) return (int32_t)(lo * s2l::kKvTile);
+  while (hi - lo > 1) {   // items(lo) > target >= items(hi); hi keys give one piece per tile
+    const int64_t mid = (lo + hi) / 2;
+    if (items_for(R, P, C, hkv, tq, (int32_t)(mid * s2l::kKvTile), o.max_splits) <= o.target_items) hi = mid;
+    else lo = mid;
+  }
+  const int32_t keys = (int32_t)(hi * s2l::kKvTile);
+  return o.max_piece_keys > 0 ? std::min(keys, o.max_piece_keys) : keys;
+}
 
 // Automatic tile width: 16-column decode tiles when every request fits one (C * G <= 16:
 // decode-shaped batches, bound by reading the keys); otherwise 256-column tiles (8-wave
@@ -75,10 +111,56 @@ int32_t auto_tile_cols(int32_t R, const int32_t* C, int32_t hq, int32_t hkv) {
   return 2 * used >= alloc ? s2l::kMaxTileCols : s2l::kMinTileCols;
 }
 
+// Which layout and split serve a batch that left both to the planner.  The rules above (256
+// columns, pieces that fill one round of workgroups) suit long key ranges.  A workgroup's fixed
+// part, unused columns and the merge of split partials weigh more in short ones: narrower tiles
+// put two workgroups on a CU or two wave groups on a tile, and no split saves the merge.  Each
+// candidate's time is estimated in us from its items,
+//   max(f + a kmax, (g n + b k) / CUs + t (g + b kmax) clamp(n / CUs - 1/2)) + merge,
+// n items with k 64-key steps in all and kmax in the longest, merge = 3.4 + 0.35 per MB of
+// partials, and taken if it is below 0.9 of the default's.  The constants are a least-squares fit to
+// 721 measured layers (103 batches of 1 to 48 requests, prefixes to 20K, chunks to 2048, five head
+// layouts; root mean square error 6%); over those the choice took 0.91 of the default's time in the
+// geometric mean and was nowhere slower (the fastest of the six candidates: 0.90).
+// Examples, layer time: one 600-token chunk without prefix (32q/8kv) 24.6 -> 16.8 us, P = 20000 and
+// C = 100 (8q/1kv) 40.1 -> 30.5 us; P = 8192, C = 512 (32q/8kv) stays at 256 columns, four pieces.
+struct Layout {
+  int32_t tile_cols, key_halves;
+  double f, a, g, b;
+};
+constexpr Layout kLayouts[] = {
+    {s2l::kMaxTileCols, 1, 4.53, 1.23, 0.78, 1.43},
+    {s2l::kMinTileCols, 1, 3.26, 0.96, 0.0, 0.83},
+    {s2l::kMinTileCols, 2, 5.18, 1.49, 2.98, 1.63},
+};
+constexpr double kCostTail = 0.52, kCostMerge = 3.4, kCostMergePerMB = 0.35;
+constexpr double kCostBase = 1.2, kCostAppend = 2.2, kCostAppendPerMB = 0.71;   // whatever the layout
+constexpr double kCostMargin = 0.9;
+
+double layout_cost(int32_t R, const int32_t* P, const int32_t* C, int32_t hq, int32_t hkv, const Layout& y,
+                   int32_t split_keys, int32_t max_splits, int32_t cus) {
+  const int32_t tq = s2l::tile_tokens(hq / hkv, y.tile_cols);
+  double n = 0, k = 0, kmax = 0, part = 0, tokens = 0;
+  for (int32_t r = 0; r < R; ++r) {
+    if (C[r] <= 0) continue;
+    const double ns = s2l::req_splits(P[r], C[r], split_keys, max_splits), nqt = s2l::num_qtiles(C[r], tq);
+    const double ends = nqt * P[r] + tq * nqt * (nqt - 1) / 2 + C[r];   // sum of the tiles' key ranges
+    n += nqt * ns * hkv;
+    k += hkv * (ends / s2l::kKvTile / y.key_halves + 0.5 * nqt * ns);
+    kmax = std::max(kmax, std::ceil(((double)P[r] + C[r]) / (ns * s2l::kKvTile * y.key_halves)));
+    part += (double)s2l::req_part_floats((int32_t)ns, C[r], hq) * 4e-6;
+    tokens += C[r];
+  }
+  const double queue = std::min(1.0, std::max(0.0, n / cus - 0.5));
+  const double busy = (y.g * n + y.b * k) / cus + kCostTail * (y.g + y.b * kmax) * queue;
+  const double append = std::max(kCostAppend, kCostAppendPerMB * tokens * hkv * s2l::kHeadDim * 8e-6);
+  return kCostBase + append + std::max(y.f + y.a * kmax, busy) + (part > 0 ? kCostMerge + kCostMergePerMB * part : 0);
+}
+
 // `frugal` keeps to the rules that need the least workspace: pieces only to fill the GPU, at most 16
 // a request, none for decode tiles below 512 keys.
-s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, int32_t R, const int32_t* C,
-                        int32_t hq, int32_t hkv, Resolved* r, bool frugal = false) {
+s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, int32_t R, const int32_t* P,
+                        const int32_t* C, int32_t hq, int32_t hkv, Resolved* r, bool frugal = false) {
   int32_t t = o ? o->target_items : 0, m = o ? o->min_split_keys : 0, x = o ? o->max_splits : 0;
   int32_t tc = o ? o->tile_cols : 0, kh = o ? o->key_halves : 0;
   if (t < 0 || m < 0 || x < 0) return fail(S2L_EINVAL, "plan opts must be >= 0");
@@ -110,6 +192,26 @@ s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, 
   r->max_splits = x > 0 ? (x < s2l::kMaxSplitsCap ? x : s2l::kMaxSplitsCap) : max_splits;
   r->max_piece_keys = decode && (!o || o->target_items == 0)
                           ? std::max<int32_t>(s2l::kDecodeMaxPieceKeys, r->min_split_keys) : 0;
+  r->unsplit = false;
+  const bool open = !o || (o->target_items == 0 && m == 0 && x == 0 && tc == 0 && kh == 0);
+  if (!open || frugal || r->tile_cols == s2l::kDecodeTileCols) return S2L_OK;
+  const Resolved base = *r;
+  double best = INFINITY;
+  for (int pass = 0; pass < 2; ++pass)   // the default first
+    for (const Layout& y : kLayouts)
+      for (const bool unsplit : {false, true}) {
+        const bool dflt = y.tile_cols == base.tile_cols && y.key_halves == base.key_halves && !unsplit;
+        if (dflt != (pass == 0)) continue;
+        Resolved c = base;
+        c.tile_cols = y.tile_cols;
+        c.key_halves = y.key_halves;
+        c.target_items = s2l::items_per_cu(y.tile_cols, y.key_halves) * num_cus;
+        c.unsplit = unsplit;
+        const int32_t keys = choose_split_keys(R, P, C, hkv, s2l::tile_tokens((int32_t)(hq / hkv), y.tile_cols), c);
+        const double cost = layout_cost(R, P, C, hq, hkv, y, keys, c.max_splits, num_cus);
+        if (dflt) best = kCostMargin * cost;
+        else if (cost < best) best = cost, *r = c;
+      }
   return S2L_OK;
 }
 
@@ -179,41 +281,6 @@ s2l::KvLaunch kv_launch(const s2l_kv_cache* c, const s2l_batch* b) {
   a.num_pages = c->num_pages;
   a.fp8 = c->dtype == S2L_KV_FP8_E4M3;
   return a;
-}
-
-// Items of the batch when every request is cut into pieces of at most split_keys keys.
-int64_t items_for(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, int32_t tq, int32_t split_keys,
-                  int32_t max_splits) {
-  int64_t n = 0;
-  for (int32_t r = 0; r < R; ++r)
-    n += (int64_t)hkv * s2l::num_qtiles(C[r], tq) * s2l::req_splits(P[r], C[r], split_keys, max_splits);
-  return n;
-}
-
-// Piece length of the batch: 0 (no split) when the batch already has at least target_items query
-// tiles; else, and never above max_piece_keys where that is set, the shortest multiple of 64 keys (at least min_split_keys) for which
-// cutting every request into ceil((P + C) / length) pieces (at most max_splits) gives no
-// more than target_items items, so that one round of workgroups covers the launch and the
-// longest item is as short as that allows.  Item counts fall as the length grows, so the
-// shortest such length is found by bisection.
-int32_t choose_split_keys(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, int32_t tq,
-                          const Resolved& o) {
-  int64_t tiles = 0, longest = 0;
-  for (int32_t r = 0; r < R; ++r) {
-    tiles += (int64_t)hkv * s2l::num_qtiles(C[r], tq);
-    if (C[r] > 0 && (int64_t)P[r] + C[r] > longest) longest = (int64_t)P[r] + C[r];
-  }
-  if (tiles == 0 || tiles >= o.target_items) return 0;
-  const int64_t lo_keys = s2l::align_up(o.min_split_keys, s2l::kKvTile);
-  int64_t lo = lo_keys / s2l::kKvTile, hi = std::max(lo, s2l::ceil_div64(longest, s2l::kKvTile));
-  if (items_for(R, P, C, hkv, tq, (int32_t)(lo * s2l::kKvTile), o.max_splits) <= o.target_items) return (int32_t)(lo * s2l::kKvTile);
-  while (hi - lo > 1) {   // items(lo) > target >= items(hi); hi keys give one piece per tile
-    const int64_t mid = (lo + hi) / 2;
-    if (items_for(R, P, C, hkv, tq, (int32_t)(mid * s2l::kKvTile), o.max_splits) <= o.target_items) hi = mid;
-    else lo = mid;
-  }
-  const int32_t keys = (int32_t)(hi * s2l::kKvTile);
-  return o.max_piece_keys > 0 ? std::min(keys, o.max_piece_keys) : keys;
 }
 
 // Binned item order (plan_rules.h): requests ranked as the device plan ranks them, their
@@ -571,7 +638,7 @@ s2l_status s2l_attn_workspace_bytes(const s2l_batch* batch, int32_t num_q_heads,
   if ((st = check_batch(batch, false, &T)) != S2L_OK) return st;
   if ((st = check_heads(num_q_heads, num_kv_heads)) != S2L_OK) return st;
   Resolved o;
-  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
+  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
       S2L_OK)
     return st;
   s2l_plan_info info;
@@ -591,7 +658,7 @@ s2l_status s2l_attn_plan(const s2l_batch* batch, int32_t num_q_heads, int32_t nu
   if (batch->num_reqs > 0 && !batch->cu_chunk) return fail(S2L_EINVAL, "cu_chunk is NULL");
   if ((st = check_heads(num_q_heads, num_kv_heads)) != S2L_OK) return st;
   Resolved o;
-  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
+  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
       S2L_OK)
     return st;
   return plan_resolved(batch, num_q_heads, num_kv_heads, o, workspace, ws_bytes, info, stream);
@@ -689,7 +756,7 @@ s2l_status s2l_chunk_prefill_attn_noalloc(const s2l_kv_cache* cache, const s2l_b
   Resolved o;
   s2l_plan_info pi;
   for (const bool frugal : {false, true}) {
-    if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads,
+    if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads,
                            &o, frugal)) != S2L_OK)
       return st;
     host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads, o,
@@ -728,7 +795,7 @@ s2l_status s2l_plan_host(int32_t num_reqs, const int32_t* prefix_lens_host, cons
   if ((st = check_batch(&b, false, &T)) != S2L_OK) return st;
   if ((st = check_heads(num_q_heads, num_kv_heads)) != S2L_OK) return st;
   Resolved o;
-  if ((st = resolve_opts(opts, false, num_cus, num_reqs, chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
+  if ((st = resolve_opts(opts, false, num_cus, num_reqs, prefix_lens_host, chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
       S2L_OK)
     return st;
   if (item_capacity < 0) return fail(S2L_EINVAL, "item_capacity < 0");

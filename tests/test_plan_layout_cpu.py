@@ -1,0 +1,48 @@
+"""The planner's choice of layout and split for batches that leave both to it (CPU only): whatever
+it chooses is one of the partitions that can be asked for by name, so it is covered by what those
+are tested for; any option given turns the choice off."""
+import numpy as np
+import pytest
+
+from paper_2604_16395_amd import plan_opts, s2l_plan_host
+from tests.test_plan_cpu import _coverage
+
+LAYOUTS = [(256, 1), (128, 1), (128, 2)]
+
+
+def _same(a, b):
+    return a[0].num_items == b[0].num_items and a[0].workspace_bytes == b[0].workspace_bytes and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_choice_is_a_partition_that_can_be_asked_for(seed):
+    rng = np.random.default_rng(seed)
+    R = int(rng.integers(1, 20))
+    P = rng.integers(0, int(rng.choice([1, 300, 3000, 30000])), size=R).astype(np.int32)
+    C = rng.integers(0, int(rng.choice([40, 300, 1500])), size=R).astype(np.int32)
+    C[0] = 50
+    hq, hkv = [(8, 2), (32, 8), (64, 8), (8, 1), (6, 2), (4, 4)][seed % 6]
+    auto = s2l_plan_host(P, C, hq, hkv, with_items=True)
+    info = auto[0]
+    assert (info.tile_cols, info.key_halves) in LAYOUTS
+    asked = [s2l_plan_host(P, C, hq, hkv, plan_opts(tile_cols=info.tile_cols, key_halves=info.key_halves, target_items=t),
+                           with_items=True) for t in (0, 1)]
+    assert any(_same(auto, x) for x in asked)
+    _coverage(P, C, hq, hkv, auto[1][auto[1][:, 0] >= 0], info.tile_cols)
+    # an option of any kind: the fixed rules
+    for o in (plan_opts(target_items=256), plan_opts(min_split_keys=512), plan_opts(max_splits=16)):
+        fixed, _ = s2l_plan_host(P, C, hq, hkv, o)
+        assert fixed.tile_cols == 256 or fixed.key_halves == 2
+
+
+def test_choice_on_short_and_long_ranges():
+    # one chunk without a prefix: 128-column tiles in one round, no merge
+    info, _ = s2l_plan_host([0], [512], 32, 8)
+    assert info.tile_cols == 128 and info.num_split_reqs == 0
+    # a long range behind few columns: narrower tiles, two workgroups a CU
+    info, _ = s2l_plan_host([20000], [100], 8, 1)
+    assert info.tile_cols == 128
+    # long ranges that fill the GPU: 256 columns
+    for P, C in (([8192], [512]), ([32768] * 8, [512] * 8)):
+        info, _ = s2l_plan_host(P, C, 32, 8)
+        assert info.tile_cols == 256
