@@ -136,7 +136,24 @@ def s2l_abi_version():
     return _lib.lib().s2l_abi_version()
 
 
+_native = None
+
+
+def _load_native():
+    """The native marshalling of the calls that every step makes.  Its functions return None for
+    arguments that are not of the plain form it expects; the ctypes path then takes them (or says
+    what is wrong with them)."""
+    global _native
+    if _native is None:
+        _native = _lib.binding((torch.Tensor, PagedKVCache, Batch, torch.bfloat16, torch.float32, torch.uint8,
+                                torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream))
+    return _native
+
+
 def s2l_kv_append(cache, batch, k_new, v_new, stream=None):
+    st = (_native or _load_native()).append(cache, batch, k_new, v_new, stream)
+    if st is not None:
+        return _lib.failed("s2l_kv_append", st) if st else None
     _check(k_new, torch.bfloat16, "k_new")
     _check(v_new, torch.bfloat16, "v_new")
     cc, bc = cache.c(), batch.c()
@@ -202,9 +219,12 @@ def s2l_attn_workspace_bytes(batch, num_q_heads, num_kv_heads, opts=None):
 
 
 def s2l_attn_plan(batch, num_q_heads, num_kv_heads, workspace, opts=None, stream=None):
+    info = s2l_plan_info()
+    st = (_native or _load_native()).plan(batch, num_q_heads, num_kv_heads, opts, workspace, info, stream)
+    if st is not None:
+        return _lib.failed("s2l_attn_plan", st) if st else info
     _check(workspace, torch.uint8, "workspace")
     bc = batch.c()
-    info = s2l_plan_info()
     _lib.call("s2l_attn_plan", ctypes.byref(bc), num_q_heads, num_kv_heads, _opts_ptr(opts),
               _ptr(workspace), workspace.numel(), ctypes.byref(info), _stream(stream))
     return info
@@ -222,7 +242,14 @@ def plan_status(workspace):
     return workspace[PLAN_STATUS_OFFSET:PLAN_STATUS_OFFSET + 4].view(torch.int32)[0]
 
 
+_ATTN = {"s2l_chunk_prefill_attn": 0, "s2l_chunk_prefill_attn_q8": 1, "s2l_attn_main": 2}
+
+
 def _attn(name, cache, batch, q, num_q_heads, softmax_scale, out, lse, plan, workspace, stream):
+    st = (_native or _load_native()).attn(_ATTN[name], cache, batch, q, num_q_heads, softmax_scale, out, lse, plan,
+                                      workspace, stream)
+    if st is not None:
+        return _lib.failed(name, st) if st else None
     _check(q, torch.bfloat16, "q")
     _check(out, torch.bfloat16, "out")
     _check(lse, torch.float32, "lse")
@@ -250,6 +277,10 @@ def s2l_append_chunk_prefill_attn(cache, batch, k_new, v_new, q, num_q_heads, so
                                   workspace, stream=None):
     """s2l_kv_append + s2l_chunk_prefill_attn, in one attention launch where possible;
     returns True when the single launch was used."""
+    r = (_native or _load_native()).fused(cache, batch, q, num_q_heads, softmax_scale, out, lse, plan, workspace, stream,
+                                      k_new, v_new)
+    if r is not None:
+        return _lib.failed("s2l_append_chunk_prefill_attn", r[0]) if r[0] else r[1]
     for t, n in ((k_new, "k_new"), (v_new, "v_new"), (q, "q"), (out, "out")):
         _check(t, torch.bfloat16, n)
     _check(lse, torch.float32, "lse")
@@ -283,6 +314,9 @@ def s2l_attn_main(cache, batch, q, num_q_heads, softmax_scale, out, lse, plan, w
 
 
 def s2l_split_reduce(batch, num_q_heads, out, lse, plan, workspace, stream=None):
+    st = (_native or _load_native()).reduce(batch, num_q_heads, out, lse, plan, workspace, stream)
+    if st is not None:
+        return _lib.failed("s2l_split_reduce", st) if st else None
     _check(out, torch.bfloat16, "out")
     _check(lse, torch.float32, "lse")
     bc = batch.c()

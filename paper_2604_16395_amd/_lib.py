@@ -151,9 +151,29 @@ def lib():
     return _lib
 
 
+def failed(name, status):
+    """Raise the error of an entry point that returned `status` on this thread."""
+    raise S2LError(name, status, lib().s2l_last_error().decode())
+
+
 def call(name, *args):
     """Call an entry point; raise S2LError on a negative status."""
     st = getattr(lib(), name)(*args)
     if st != S2L_OK:
-        raise S2LError(name, st, lib().s2l_last_error().decode())
+        failed(name, st)
     return st
+
+
+def binding(objects):
+    """The native marshalling module (csrc/python/binding.cpp), bound to lib()'s entry points and
+    to `objects`, the types and functions it needs.  Fails loudly when it has not been built."""
+    handle = lib()
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise S2LLibraryMissing(
+            f"the _binding module is missing ({e}): build it with `python -m paper_2604_16395_amd.build`") from e
+    names = ("s2l_kv_append", "s2l_attn_plan", "s2l_chunk_prefill_attn", "s2l_chunk_prefill_attn_q8", "s2l_attn_main",
+             "s2l_append_chunk_prefill_attn", "s2l_split_reduce")
+    _binding.setup(objects, tuple(ctypes.cast(getattr(handle, n), c_vp).value for n in names))
+    return _binding

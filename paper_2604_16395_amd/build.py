@@ -1,4 +1,5 @@
-"""Build libs2l.so (HIP kernels for gfx950 + the C-ABI layer) in place.
+"""Build libs2l.so (HIP kernels for gfx950 + the C-ABI layer) and the Python package's native
+argument marshalling (_binding.so, CPython API) in place.
 
 Usage: python -m paper_2604_16395_amd.build [-v] [--sanitize]
 
@@ -14,6 +15,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -21,6 +23,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libs2l.so")
+BINDING = os.path.join(PKG, "_binding.so")
 ARCH = "gfx950"
 
 
@@ -49,6 +52,8 @@ def build(verbose=False):
     for src in sorted(glob.glob(os.path.join(CSRC, "*.cpp"))):
         obj = os.path.join(BUILD, os.path.basename(src) + ".o")
         jobs.append([hipcc, *COMMON, "-c", src, "-o", obj])
+    binding = [hipcc, *COMMON, "-shared", "-I", sysconfig.get_paths()["include"],
+               os.path.join(CSRC, "python", "binding.cpp"), "-o", BINDING + ".tmp"]
 
     def run(cmd):
         if verbose:
@@ -63,7 +68,8 @@ def build(verbose=False):
         return cmd[-1]
 
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
-        objs = list(ex.map(run, jobs))
+        objs = list(ex.map(run, jobs + [binding]))[:len(jobs)]
+    os.replace(BINDING + ".tmp", BINDING)
     tmp = LIB + ".tmp"
     cmd = [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     run(cmd)

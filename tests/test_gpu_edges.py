@@ -135,3 +135,46 @@ def test_device_plan_equals_the_host_plan(R, hkv):
         assert np.array_equal(real[:, 8], P[r]) and np.array_equal(real[:, 9], C[r]) and np.array_equal(real[:, 10], cu[r])
         pad = rec[rec[:, 0] < 0]
         assert len(pad) == (items[:, 0] < 0).sum() and np.all(pad[:, 0] == -1)
+
+
+def test_native_and_ctypes_marshalling_agree():
+    """The per-step calls through the native marshalling (plain arguments) and through ctypes (here
+    because the stream is a numpy integer, which only that path takes): the same launches, so the
+    same bits; on a side stream given as an object, a number or the current one; and arguments that
+    neither path takes raise the same errors."""
+    case = workloads.make_case("marshal", [512, 64], [40, 100], 32, 8, seed=56)
+    outs = []
+    side = torch.cuda.Stream()
+    for stream in (None, side, side.cuda_stream, np.int64(0)):
+        with torch.cuda.stream(side if stream is side else torch.cuda.current_stream()):
+            s = Setup(case)
+            k, v = to_bf16(s.k_new), to_bf16(s.v_new)
+            ws = torch.empty(s2l.s2l_attn_workspace_bytes(s.batch, 32, 8), dtype=torch.uint8, device=DEV)
+            out = torch.zeros((case.total_tokens, 32, 128), dtype=torch.bfloat16, device=DEV)
+            lse = torch.zeros((case.total_tokens, 32), dtype=torch.float32, device=DEV)
+            torch.cuda.synchronize()
+            plan = s2l.s2l_attn_plan(s.batch, 32, 8, ws, None, stream)
+            s2l.s2l_kv_append(s.cache, s.batch, k, v, stream)
+            s2l.s2l_chunk_prefill_attn(s.cache, s.batch, s.q, 32, SCALE, out, lse, plan, ws, stream)
+            res = [out.clone(), lse.clone(), s.cache.k_pages]
+            torch.cuda.synchronize()
+            res[0].copy_(out), res[1].copy_(lse)
+            out.zero_()
+            assert s2l.s2l_append_chunk_prefill_attn(s.cache, s.batch, k, v, s.q, 32, SCALE, out, lse, plan, ws, stream)
+            torch.cuda.synchronize()
+            res.append(out.clone())
+            out.zero_()
+            s2l.s2l_attn_main(s.cache, s.batch, s.q, 32, SCALE, out, None, plan, ws, stream)
+            s2l.s2l_split_reduce(s.batch, 32, out, None, plan, ws, stream)
+            torch.cuda.synchronize()
+            res.append(out.clone())
+            outs.append(res)
+    assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for o in outs[1:] for a, b in zip(outs[0], o))
+    assert torch.equal(outs[0][0], outs[0][3]) and torch.equal(outs[0][0], outs[0][4])
+    for bad in (k.float(), torch.empty((200, 8, 128), dtype=torch.bfloat16, device=DEV)[::2]):
+        with pytest.raises(ValueError, match="k_new must be a contiguous"):
+            s2l.s2l_kv_append(s.cache, s.batch, bad, v)
+    with pytest.raises(s2l.S2LError, match="NULL"):
+        s2l.s2l_kv_append(s.cache, s.batch, None, v)
+    with pytest.raises(s2l.S2LError, match="workspace"):
+        s2l.s2l_chunk_prefill_attn(s.cache, s.batch, s.q, 32, SCALE, out, lse, plan, ws[:100])
