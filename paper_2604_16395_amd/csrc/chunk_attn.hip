@@ -7,11 +7,11 @@
 // One workgroup = one work item of the plan: kv head g, 32 kColWaves packed query columns
 // (tq tokens x G heads, token-major) and a key range [lo, hi).  With kHalves = 2 the
 // workgroup has two groups of kColWaves waves on the same columns, each taking one half of
-// the key range (in whole 64-key tiles) with its own K/V ring; the second group hands its
-// (O, m, l) to the first through LDS at the end and the first merges them (the log-sum-exp
-// merge of the online softmax), so a key range is split in two without any partials in
-// memory.  The item's description is one 64-byte record written by the plan kernel (a
-// single scalar load).
+// the key range (in whole 64-key tiles) with its own K/V ring; at the end the groups hand each
+// other half of O and their (m, l) through LDS and merge them (the log-sum-exp
+// merge of the online softmax, each group finishing half of the dims), so a key range is split
+// in two without any partials in memory.  The item's description is one 64-byte record written
+// by the plan kernel (a single scalar load).
 //
 // Data movement.  K and V tiles of 64 keys x 128 are staged in LDS, one key row of 256
 // bytes each, 16-byte chunks permuted per row (K: chunk c of row r at c ^ (r & 15); V: at
@@ -52,8 +52,8 @@
 //
 // Unsplit items write bf16 O = acc / l (and LSE).  Split items write fp32 partials
 // (acc, m, l) that split_reduce_kernel merges (the standard log-sum-exp merge of partial
-// softmaxes); in the one-group bf16 layouts they are staged through LDS and stored as whole
-// rows with write-through stores.
+// softmaxes); where the ring can hold the tile's rows they are staged through LDS and stored as
+// whole rows with write-through stores.
 #include "launch.h"
 #include "plan_rules.h"
 #include "s2l_device.h"
@@ -186,8 +186,8 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   constexpr int kWaves = kColWaves * kHalves;
   constexpr int kS = RingT::kStages;
   static_assert(kHalves == 1 || kHalves == 2, "one or two key-range groups");
-  static_assert(kHalves == 1 || kColWaves * 32 * 128 * 4 + kColWaves * 64 * 8 <= RingT::kBytes,
-                "the second group's (O, m, l) fits in the LDS of the rings");
+  static_assert(kHalves == 1 || kColWaves * 32 * 128 * 4 + 2 * kColWaves * 64 * 8 <= RingT::kBytes,
+                "the groups' halves of O and their (m, l) fit in the LDS of the rings");
   constexpr int kQuarters = kColWaves / 4;           // waves sharing one page of a tile
   constexpr int kRowsPerWave = 16 / kQuarters;       // key rows each wave moves per tile
   constexpr int kDma = kRowsPerWave / 4;             // bf16: 1 KiB LDS-direct loads per wave
@@ -893,119 +893,145 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
 
   float l_fin = sum_with_partner(l_run);
   float m_fin = l_fin > 0.f ? m_run : -INFINITY;     // -inf: no visible key in this range
-  if constexpr (kHalves == 2) {
-    // The second group's (O, m, l) to the first through LDS (the rings are free once every
-    // wave is past its last tile): column wave cw of both groups holds the same elements in
-    // the same lanes; element group k = 4 db + j of lane l is at ((k kColWaves + cw) 64 + l)
-    // x 16 bytes, so each store or load of 64 lanes covers 1 KiB without bank conflicts.
-    __builtin_amdgcn_s_barrier();
-    float* xo = reinterpret_cast<float*>(smem);
-    float* xml = xo + 16 * kColWaves * 64 * 4;
-    if (grp == 1) {
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *reinterpret_cast<f32x4*>(xo + (((4 * db + j) * kColWaves + cw) * 64 + lane) * 4) =
-              f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
-      *reinterpret_cast<f32x2*>(xml + (cw * 64 + lane) * 2) = f32x2{m_fin, l_fin};
-    }
-    wait_lgkmcnt0();
-    __builtin_amdgcn_s_barrier();
-    if (grp == 1) return;
-    const f32x2 ml1 = *reinterpret_cast<const f32x2*>(xml + (cw * 64 + lane) * 2);
-    const float mstar = fmaxf(m_fin, ml1[0]);
-    const float a0 = merge_weight(m_fin, mstar), a1 = merge_weight(ml1[0], mstar);
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(xo + (((4 * db + j) * kColWaves + cw) * 64 + lane) * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[db][4 * j + e] = a0 * o[db][4 * j + e] + a1 * x[e];
-      }
-    l_fin = a0 * l_fin + a1 * ml1[1];
-    m_fin = mstar;
-  }
-  // Split piece, when the ring can hold the whole tile's rows (bf16 pages; one key group):
-  // the fp32 partial is staged through LDS, row-major with each row's 16-byte chunks
-  // permuted by (column mod 16) so that both the register-order writes and the row reads
-  // are free of bank conflicts, and then stored a row run at a time (the G head rows of a
-  // token are adjacent) with device-scope (sc1) stores, which write through the L2: no
-  // dirty partial lines are left for the write-back at the end of the launch.  The row sum
-  // and max follow with the same policy.
   float* const acc = partials + it.part_off;
   const int64_t acc_bytes = (int64_t)ns * C * hq * (kHeadDim + 4) * 4;
-  if (kHalves == 1 && RingT::kBytes >= kColWaves * 32 * kHeadDim * 4 && ns > 1 && acc_bytes <= 0x7fffffff) {
-    constexpr int kSc1 = 16;   // cache policy: device scope
-    __builtin_amdgcn_s_barrier();   // every wave is past its last read of the ring
-    float* xs = reinterpret_cast<float*>(smem);
+  // Outputs of dim blocks D0 .. D0 + kDb - 1 of the workgroup's columns (all four of them, or
+  // each of two groups' half).
+  constexpr int kDb = 4 / kHalves;
+  auto finish = [&](auto first_db) {
+    constexpr int D0 = decltype(first_db)::value;
+    // Split piece, when the ring can hold the whole tile's rows: the fp32 partial is staged
+    // through LDS, row-major with each row's 16-byte chunks permuted by (column mod 16) so that
+    // both the register-order writes and the row reads are free of bank conflicts, and then
+    // stored a row run at a time (the G head rows of a token are adjacent) with device-scope
+    // (sc1) stores, which write through the L2: no dirty partial lines are left for the
+    // write-back at the end of the launch.  The row sum and max follow with the same policy.
+    if (RingT::kBytes >= kColWaves * 32 * kHeadDim * 4 && ns > 1 && acc_bytes <= 0x7fffffff) {
+      constexpr int kSc1 = 16;   // cache policy: device scope
+      wait_lgkmcnt0();
+      __builtin_amdgcn_s_barrier();   // every wave is past its last read of the ring (or exchange)
+      float* xs = reinterpret_cast<float*>(smem);
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+      for (int db = D0; db < D0 + kDb; ++db)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<f32x4*>(xs + (col * 32 + ((8 * db + 2 * j + half) ^ (col & 15))) * 4) =
-            f32x4{o[db][4 * j] * v_mul, o[db][4 * j + 1] * v_mul, o[db][4 * j + 2] * v_mul,
-                  o[db][4 * j + 3] * v_mul};
+        for (int j = 0; j < 4; ++j)
+          *reinterpret_cast<f32x4*>(xs + (col * 32 + ((8 * db + 2 * j + half) ^ (col & 15))) * 4) =
+              f32x4{o[db][4 * j] * v_mul, o[db][4 * j + 1] * v_mul, o[db][4 * j + 2] * v_mul,
+                    o[db][4 * j + 3] * v_mul};
+      wait_lgkmcnt0();
+      __builtin_amdgcn_s_barrier();
+      const auto prs = make_rsrc(acc, (int32_t)acc_bytes);
+      const int ncols = min(tq * G, (i1 - i0) * G);   // the valid columns of this tile
+      // row of column c: (s C + i0 + c / G) hq + g G + c % G = rbase + c + (c / G)(hq - G)
+      const int64_t rbase = ((int64_t)it.s * C + i0) * hq + g * G;
+#pragma unroll
+      for (int u0 = 0; u0 < 32 * kColWaves * 32; u0 += kThreads) {
+        const int u = u0 + (int)threadIdx.x;
+        const int c = u >> 5, k = u & 31;   // column, 16-byte chunk
+        if (c < ncols) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(xs + (c * 32 + (k ^ (c & 15))) * 4);
+          const int64_t pr = rbase + c + (int64_t)div_g(c) * (hq - G);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), prs, (uint32_t)(pr * 512 + 16 * k), 0,
+                                                 kSc1);
+        }
+      }
+      if (valid && half == 0 && D0 == 0) {
+        const int64_t prow = ((int64_t)it.s * C + tok) * hq + hq_col;
+        const int64_t ml_off = (int64_t)ns * C * hq * kHeadDim * 4 + 16 * prow;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{m_fin, l_fin, 0.f, 0.f}), prs,
+                                               (uint32_t)ml_off, 0, kSc1);
+      }
+      return;
+    }
+    if (!valid) return;
+    if (ns == 1) {
+      const float inv = v_mul / l_fin;
+      // the lane pair holds dims 8 j + {0..3} and 8 j + {4..7} of a block: exchanged so that the
+      // lower lane stores the eight dims of an even j, the upper one those of the next j
+      uint16_t* orow = out + ((int64_t)(row0 + tok) * hq + hq_col) * 128 + 8 * half;
+#pragma unroll
+      for (int db = D0; db < D0 + kDb; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+          u32x2 w[2];   // [first, second word of the lane's four dims of j and of j + 1]
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+            w[e] = swap_halves(pack_bf16x2(o[db][4 * j + 2 * e] * inv, o[db][4 * j + 2 * e + 1] * inv),
+                               pack_bf16x2(o[db][4 * j + 4 + 2 * e] * inv, o[db][4 * j + 5 + 2 * e] * inv));
+          *reinterpret_cast<u32x4*>(orow + 32 * db + 8 * j) = u32x4{w[0][0], w[1][0], w[0][1], w[1][1]};
+        }
+      if (lse != nullptr && half == 0 && D0 == 0)
+        lse[(int64_t)(row0 + tok) * hq + hq_col] = (m_fin + __log2f(l_fin)) * kLn2;
+      return;
+    }
+    // Split piece (else): fp32 partial (acc row, then (m, l, 0, 0)), stored from the registers; a
+    // column with no visible key in this piece has (-inf, 0): the merge skips it.
+    float* ml = acc + (int64_t)ns * C * hq * kHeadDim;
+    const int64_t prow = ((int64_t)it.s * C + tok) * hq + hq_col;
+    float* arow = acc + prow * kHeadDim + 4 * half;
+#pragma unroll
+    for (int db = D0; db < D0 + kDb; ++db)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 w = {o[db][4 * j] * v_mul, o[db][4 * j + 1] * v_mul, o[db][4 * j + 2] * v_mul,
+                         o[db][4 * j + 3] * v_mul};
+        *reinterpret_cast<f32x4*>(arow + 32 * db + 8 * j) = w;
+      }
+    if (half == 0 && D0 == 0) *reinterpret_cast<f32x4*>(ml + 4 * prow) = f32x4{m_fin, l_fin, 0.f, 0.f};
+  };
+  constexpr std::integral_constant<int, 0> kFirstDims{};
+  if constexpr (kHalves == 1) {
+    finish(kFirstDims);
+  } else {
+    // The groups' (O, m, l) merged through LDS (the rings are free once every wave is past its
+    // last tile), each group finishing half of the dims: it hands the other its (m, l) and the
+    // other's half of O.  Column wave cw of both groups holds the same elements in the same lanes;
+    // element group k = 4 db + j of lane l is at ((k kColWaves + cw) 64 + l) x 16 bytes, so each
+    // store or load of 64 lanes covers 1 KiB without bank conflicts.  (Against one group handing
+    // over all of O and ending, and the other storing it from its registers: two pieces of P = 512,
+    // C = 512, 32q/8kv 15.2 -> 12.8 us, of P = 5003, C = 389, 16q/4kv 25.3 -> 22.9; unsplit
+    // launches 0.1 us less.)
     wait_lgkmcnt0();
     __builtin_amdgcn_s_barrier();
-    const auto prs = make_rsrc(acc, (int32_t)acc_bytes);
-    const int ncols = min(tq * G, (i1 - i0) * G);   // the valid columns of this tile
-    // row of column c: (s C + i0 + c / G) hq + g G + c % G = rbase + c + (c / G)(hq - G)
-    const int64_t rbase = ((int64_t)it.s * C + i0) * hq + g * G;
+    float* xo = reinterpret_cast<float*>(smem);
+    float* xml = xo + 16 * kColWaves * 64 * 4;   // [group][cw][lane][2]
+    auto at = [&](int k) { return reinterpret_cast<f32x4*>(xo + ((k * kColWaves + cw) * 64 + lane) * 4); };
+    auto hand_over = [&](auto first_db) {
+      constexpr int D0 = decltype(first_db)::value;
 #pragma unroll
-    for (int u0 = 0; u0 < 32 * kColWaves * 32; u0 += kThreads) {
-      const int u = u0 + (int)threadIdx.x;
-      const int c = u >> 5, k = u & 31;   // column, 16-byte chunk
-      if (c < ncols) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(xs + (c * 32 + (k ^ (c & 15))) * 4);
-        const int64_t pr = rbase + c + (int64_t)div_g(c) * (hq - G);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), prs, (uint32_t)(pr * 512 + 16 * k), 0,
-                                               kSc1);
-      }
-    }
-    if (valid && half == 0) {
-      const int64_t prow = ((int64_t)it.s * C + tok) * hq + hq_col;
-      const int64_t ml_off = (int64_t)ns * C * hq * kHeadDim * 4 + 16 * prow;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{m_fin, l_fin, 0.f, 0.f}), prs,
-                                             (uint32_t)ml_off, 0, kSc1);
-    }
-    return;
+      for (int db = D0; db < D0 + kDb; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          *at(4 * db + j) = f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
+    };
+    constexpr std::integral_constant<int, 2> kLastDims{};
+    if (grp == 0) hand_over(kLastDims);
+    else hand_over(kFirstDims);
+    *reinterpret_cast<f32x2*>(xml + ((grp * kColWaves + cw) * 64 + lane) * 2) = f32x2{m_fin, l_fin};
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+    const f32x2 ml0 = *reinterpret_cast<const f32x2*>(xml + (cw * 64 + lane) * 2);
+    const f32x2 ml1 = *reinterpret_cast<const f32x2*>(xml + ((kColWaves + cw) * 64 + lane) * 2);
+    const float mstar = fmaxf(ml0[0], ml1[0]);
+    const float a0 = merge_weight(ml0[0], mstar), a1 = merge_weight(ml1[0], mstar);
+    l_fin = a0 * ml0[1] + a1 * ml1[1];
+    m_fin = mstar;
+    const float own = grp == 0 ? a0 : a1, other = grp == 0 ? a1 : a0;
+    auto merge = [&](auto first_db) {
+      constexpr int D0 = decltype(first_db)::value;
+#pragma unroll
+      for (int db = D0; db < D0 + kDb; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4 x = *at(4 * db + j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[db][4 * j + e] = own * o[db][4 * j + e] + other * x[e];
+        }
+      finish(first_db);
+    };
+    if (grp == 0) merge(kFirstDims);
+    else merge(kLastDims);
   }
-  if (!valid) return;
-  if (ns == 1) {
-    const float inv = v_mul / l_fin;
-    // the lane pair holds dims 8 j + {0..3} and 8 j + {4..7} of a block: exchanged so that the
-    // lower lane stores the eight dims of an even j, the upper one those of the next j
-    uint16_t* orow = out + ((int64_t)(row0 + tok) * hq + hq_col) * 128 + 8 * half;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        u32x2 w[2];   // [first, second word of the lane's four dims of j and of j + 1]
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-          w[e] = swap_halves(pack_bf16x2(o[db][4 * j + 2 * e] * inv, o[db][4 * j + 2 * e + 1] * inv),
-                             pack_bf16x2(o[db][4 * j + 4 + 2 * e] * inv, o[db][4 * j + 5 + 2 * e] * inv));
-        *reinterpret_cast<u32x4*>(orow + 32 * db + 8 * j) = u32x4{w[0][0], w[1][0], w[0][1], w[1][1]};
-      }
-    if (lse != nullptr && half == 0) lse[(int64_t)(row0 + tok) * hq + hq_col] = (m_fin + __log2f(l_fin)) * kLn2;
-    return;
-  }
-  // Split piece (other layouts): fp32 partial (acc row, then (m, l, 0, 0)), stored from the
-  // registers; a column with no visible key in this piece has (-inf, 0): the merge skips it.
-  float* ml = acc + (int64_t)ns * C * hq * kHeadDim;
-  const int64_t prow = ((int64_t)it.s * C + tok) * hq + hq_col;
-  float* arow = acc + prow * kHeadDim + 4 * half;
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f32x4 w = {o[db][4 * j] * v_mul, o[db][4 * j + 1] * v_mul, o[db][4 * j + 2] * v_mul,
-                       o[db][4 * j + 3] * v_mul};
-      *reinterpret_cast<f32x4*>(arow + 32 * db + 8 * j) = w;
-    }
-  if (half == 0) *reinterpret_cast<f32x4*>(ml + 4 * prow) = f32x4{m_fin, l_fin, 0.f, 0.f};
 }
 
 // Merge of split partials: workgroup (row, y) merges heads 8y .. 8y+7 of one chunk row; a half
