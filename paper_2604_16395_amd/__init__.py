@@ -145,7 +145,8 @@ def _load_native():
     what is wrong with them)."""
     global _native
     if _native is None:
-        _native = _lib.binding((torch.Tensor, PagedKVCache, Batch, torch.bfloat16, torch.float32, torch.uint8,
+        _native = _lib.binding((torch.Tensor, PagedKVCache, Batch, s2l_plan_opts, s2l_plan_info, torch.cuda.Stream,
+                                torch.bfloat16, torch.float32, torch.uint8,
                                 torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream))
     return _native
 

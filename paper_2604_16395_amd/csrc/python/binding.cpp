@@ -24,7 +24,7 @@ struct Entry {
   s2l_status (*reduce)(const s2l_batch*, int32_t, void*, float*, const s2l_plan_info*, const void*, size_t, void*);
 } lib;
 
-PyObject *tensor_type, *cache_type, *batch_type, *bf16, *f32, *u8, *is_initialized, *get_device, *get_stream;
+PyObject *tensor_type, *cache_type, *batch_type, *opts_type, *info_type, *stream_type, *bf16, *f32, *u8, *is_initialized, *get_device, *get_stream;
 PyObject *s_dtype, *s_data_ptr, *s_is_contiguous, *s_shape, *s_numel, *s_k_pages, *s_v_pages, *s_k_scale, *s_v_scale,
     *s_fp8, *s_prefix_host, *s_chunk_host, *s_tables_host, *s_prefix_lens, *s_chunk_lens, *s_cu_chunk, *s_block_tables,
     *s_cuda_stream;
@@ -136,7 +136,7 @@ bool cache_arg(PyObject* o, s2l_kv_cache* c) {
   return true;
 }
 
-// None: the current stream of the current device; a number; or a stream object.
+// None: the current stream of the current device; a number; or a torch.cuda.Stream.
 bool stream_arg(PyObject* s, void** p) {
   if (s == Py_None) {
     const Ref ready(PyObject_CallNoArgs(is_initialized));
@@ -147,11 +147,12 @@ bool stream_arg(PyObject* s, void** p) {
     return raw && to_ptr(raw.o, p);
   }
   if (PyLong_CheckExact(s)) return to_ptr(s, p);
+  if (PyObject_IsInstance(s, stream_type) != 1) return false;
   const Ref raw(PyObject_GetAttr(s, s_cuda_stream));
   return raw && PyLong_CheckExact(raw.o) && to_ptr(raw.o, p);
 }
 
-// A ctypes structure of exactly `size` bytes; None only where allowed.
+// A ctypes structure of exactly this type; None only where allowed.
 template <typename T>
 struct StructArg {
   Py_buffer b{};
@@ -160,9 +161,9 @@ struct StructArg {
   ~StructArg() {
     if (held) PyBuffer_Release(&b);
   }
-  bool take(PyObject* o, bool none_ok = false) {
+  bool take(PyObject* o, PyObject* type, bool none_ok = false) {
     if (o == Py_None) return none_ok;
-    if (PyObject_GetBuffer(o, &b, PyBUF_WRITABLE) != 0) return false;
+    if ((PyObject*)Py_TYPE(o) != type || PyObject_GetBuffer(o, &b, PyBUF_WRITABLE) != 0) return false;
     held = true;
     p = static_cast<T*>(b.buf);
     return b.len == (Py_ssize_t)sizeof(T);
@@ -208,8 +209,8 @@ PyObject* plan(PyObject*, PyObject* const* a, Py_ssize_t n) {
   int32_t hq, hkv;
   void *ws, *stream;
   size_t bytes;
-  if (n != 7 || !batch.take(a[0]) || !int_arg(a[1], &hq) || !int_arg(a[2], &hkv) || !opts.take(a[3], true) ||
-      !tensor(a[4], u8, &ws) || !numel(a[4], &bytes) || !info.take(a[5]) || !stream_arg(a[6], &stream))
+  if (n != 7 || !batch.take(a[0]) || !int_arg(a[1], &hq) || !int_arg(a[2], &hkv) || !opts.take(a[3], opts_type, true) ||
+      !tensor(a[4], u8, &ws) || !numel(a[4], &bytes) || !info.take(a[5], info_type) || !stream_arg(a[6], &stream))
     return general();
   return call([&] { return lib.plan(&batch.c, hq, hkv, opts.p, ws, bytes, info.p, stream); });
 }
@@ -226,7 +227,7 @@ struct AttnArgs {
   bool take(PyObject* const* a) {
     if (!tensor(a[2], bf16, &q) || !tensor(a[5], bf16, &out) || !tensor(a[6], f32, &lse, true) ||
         !tensor(a[8], u8, &ws) || !numel(a[8], &bytes) || !cache_arg(a[0], &cache) || !batch.take(a[1]) ||
-        !int_arg(a[3], &hq) || !PyFloat_CheckExact(a[4]) || !plan.take(a[7]) || !stream_arg(a[9], &stream))
+        !int_arg(a[3], &hq) || !PyFloat_CheckExact(a[4]) || !plan.take(a[7], info_type) || !stream_arg(a[9], &stream))
       return false;
     scale = (float)PyFloat_AS_DOUBLE(a[4]);
     return true;
@@ -264,7 +265,7 @@ PyObject* reduce(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void *out, *lse, *ws, *stream;
   size_t bytes;
   if (n != 7 || !tensor(a[2], bf16, &out) || !tensor(a[3], f32, &lse, true) || !tensor(a[5], u8, &ws) ||
-      !numel(a[5], &bytes) || !batch.take(a[0]) || !int_arg(a[1], &hq) || !info.take(a[4]) || !stream_arg(a[6], &stream))
+      !numel(a[5], &bytes) || !batch.take(a[0]) || !int_arg(a[1], &hq) || !info.take(a[4], info_type) || !stream_arg(a[6], &stream))
     return general();
   return call([&] { return lib.reduce(&batch.c, hq, out, static_cast<float*>(lse), info.p, ws, bytes, stream); });
 }
@@ -272,14 +273,15 @@ PyObject* reduce(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (types and dtypes and torch functions as a tuple, entry point addresses as a tuple)
 PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void* f[7];
-  PyObject** o[] = {&tensor_type, &cache_type, &batch_type, &bf16, &f32, &u8, &is_initialized, &get_device, &get_stream};
-  if (n != 2 || !PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != 9 || !PyTuple_Check(a[1]) || PyTuple_GET_SIZE(a[1]) != 7) {
+  PyObject** o[] = {&tensor_type, &cache_type, &batch_type, &opts_type, &info_type, &stream_type,
+                    &bf16, &f32, &u8, &is_initialized, &get_device, &get_stream};
+  if (n != 2 || !PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != 12 || !PyTuple_Check(a[1]) || PyTuple_GET_SIZE(a[1]) != 7) {
     PyErr_SetString(PyExc_TypeError, "setup(objects, addresses)");
     return nullptr;
   }
   for (int i = 0; i < 7; ++i)
     if (!to_ptr(PyTuple_GET_ITEM(a[1], i), &f[i])) return nullptr;
-  for (int i = 0; i < 9; ++i) {
+  for (int i = 0; i < 12; ++i) {
     Py_INCREF(PyTuple_GET_ITEM(a[0], i));
     Py_XSETREF(*o[i], PyTuple_GET_ITEM(a[0], i));
   }
