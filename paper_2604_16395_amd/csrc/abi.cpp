@@ -67,8 +67,8 @@ int64_t items_for(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, in
 }
 
 // Piece length of the batch: 0 (no split) when the batch already has at least target_items query
-// tiles; else, and never above max_piece_keys where that is set, the shortest multiple of 64 keys (at least min_split_keys) for which
-// cutting every request into ceil((P + C) / length) pieces (at most max_splits) gives no
+// tiles; else, and never above max_piece_keys where that is set, the shortest multiple of 64
+// keys (at least min_split_keys) for which cutting every request into ceil((P + C) / length) pieces (at most max_splits) gives no
 // more than target_items items, so that one round of workgroups covers the launch and the
 // longest item is as short as that allows.  Item counts fall as the length grows, so the
 // shortest such length is found by bisection.
@@ -638,8 +638,8 @@ s2l_status s2l_attn_workspace_bytes(const s2l_batch* batch, int32_t num_q_heads,
   if ((st = check_batch(batch, false, &T)) != S2L_OK) return st;
   if ((st = check_heads(num_q_heads, num_kv_heads)) != S2L_OK) return st;
   Resolved o;
-  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
-      S2L_OK)
+  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads,
+                         num_kv_heads, &o)) != S2L_OK)
     return st;
   s2l_plan_info info;
   host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, num_kv_heads, o, &info,
@@ -658,8 +658,8 @@ s2l_status s2l_attn_plan(const s2l_batch* batch, int32_t num_q_heads, int32_t nu
   if (batch->num_reqs > 0 && !batch->cu_chunk) return fail(S2L_EINVAL, "cu_chunk is NULL");
   if ((st = check_heads(num_q_heads, num_kv_heads)) != S2L_OK) return st;
   Resolved o;
-  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
-      S2L_OK)
+  if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads,
+                         num_kv_heads, &o)) != S2L_OK)
     return st;
   return plan_resolved(batch, num_q_heads, num_kv_heads, o, workspace, ws_bytes, info, stream);
 }
@@ -756,8 +756,8 @@ s2l_status s2l_chunk_prefill_attn_noalloc(const s2l_kv_cache* cache, const s2l_b
   Resolved o;
   s2l_plan_info pi;
   for (const bool frugal : {false, true}) {
-    if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads,
-                           &o, frugal)) != S2L_OK)
+    if ((st = resolve_opts(opts, true, 0, batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host,
+                           num_q_heads, cache->num_kv_heads, &o, frugal)) != S2L_OK)
       return st;
     host_plan(batch->num_reqs, batch->prefix_lens_host, batch->chunk_lens_host, num_q_heads, cache->num_kv_heads, o,
               &pi, nullptr, 0);
@@ -795,8 +795,8 @@ s2l_status s2l_plan_host(int32_t num_reqs, const int32_t* prefix_lens_host, cons
   if ((st = check_batch(&b, false, &T)) != S2L_OK) return st;
   if ((st = check_heads(num_q_heads, num_kv_heads)) != S2L_OK) return st;
   Resolved o;
-  if ((st = resolve_opts(opts, false, num_cus, num_reqs, prefix_lens_host, chunk_lens_host, num_q_heads, num_kv_heads, &o)) !=
-      S2L_OK)
+  if ((st = resolve_opts(opts, false, num_cus, num_reqs, prefix_lens_host, chunk_lens_host, num_q_heads, num_kv_heads,
+                         &o)) != S2L_OK)
     return st;
   if (item_capacity < 0) return fail(S2L_EINVAL, "item_capacity < 0");
   host_plan(num_reqs, prefix_lens_host, chunk_lens_host, num_q_heads, num_kv_heads, o, info, items_out,
