@@ -30,7 +30,8 @@
 //
 // Compute, per wave (32 query columns, one per lane pair), per 32-key sub-block b:
 //   * S^T(b) = K Q^T with v_mfma_f32_32x32x16_bf16: A = K rows from LDS, B = Q held in
-//     registers (read once through the ring's LDS, before its later tiles need it), so every lane owns one query column and 16 of the sub-block's scores;
+//     registers (read once through the ring's LDS, before its later tiles need it), so every
+//     lane owns one query column and 16 of the sub-block's scores;
 //   * online softmax in the exp2 domain against a per-column reference m, set to the exact
 //     max of the item's first sub-block (lane pair combined by v_permlane32_swap); later
 //     probabilities exp2(s c - m) are accumulated against it as they come, so a sub-block
@@ -52,8 +53,7 @@
 //
 // Unsplit items write bf16 O = acc / l (and LSE).  Split items write fp32 partials
 // (acc, m, l) that split_reduce_kernel merges (the standard log-sum-exp merge of partial
-// softmaxes); where the ring can hold the tile's rows they are staged through LDS and stored as
-// whole rows with write-through stores.
+// softmaxes), staged through LDS and stored as whole rows with write-through stores.
 #include "launch.h"
 #include "plan_rules.h"
 #include "s2l_device.h"
@@ -165,12 +165,15 @@ __device__ inline float merge_weight(float m_s, float mstar) {
 }
 
 // LDS of one group of waves: a K/V ring of kStages 16 KiB tiles each (four stages for the
-// 8-column-wave bf16 kernel, which runs alone on its CU; two otherwise).
+// 8-column-wave bf16 kernel, which runs alone on its CU; two otherwise), or the fp32 rows of a
+// split tile where those are larger (the 8-column-wave e4m3 kernel, whose registers allow one
+// workgroup a CU anyway).
 template <bool kFp8, int kColWaves, int kHalves>
 struct Ring {
   static constexpr int kStages = (!kFp8 && kColWaves == 8) ? 4 : 2;
   static constexpr int kGroupBytes = 2 * kStages * kTileBytes;
-  static constexpr int kBytes = kHalves * kGroupBytes;
+  static constexpr int kTileRows = kColWaves * 32 * kHeadDim * 4;
+  static constexpr int kBytes = kHalves * kGroupBytes > kTileRows ? kHalves * kGroupBytes : kTileRows;
 };
 
 template <bool kFp8, int kColWaves, int kHalves, bool kFused, bool kQ8>
@@ -374,8 +377,9 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   // win0 + l (clamped as above).  Each 64-tile window is copied into one of this wave's two
   // LDS slots (the first into slot 1) by an LDS-direct load, 64 tiles before it is needed for
   // all but the first; the per-iteration vmcnt waits cover it (it is older than the copies
-  // they wait for), and it is read into pg_win when the window moves on.  Page ids never come from scalar loads inside the loop: those share lgkmcnt with the LDS reads,
-  // whose waits would then all be full waits.
+  // they wait for), and it is read into pg_win when the window moves on.  Page ids never come
+  // from scalar loads inside the loop: those share lgkmcnt with the LDS reads, whose waits would
+  // then all be full waits.
   const i32x4 bt_rs = sgpr_rsrc(bt, 4 * (last_page + 1));
   auto win_offset = [&](int w0) -> uint32_t {
     const int idx = (lo >> 4) + 4 * (w0 + lane) + pw;
@@ -569,6 +573,23 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
       slot_schedule<kQK, true>();
       slot_schedule<kQK, kNext>();
       slot_schedule<kQK, kNext>();
+    } else {
+      // A score MFMA here takes 64 cycles and serves half of the step, so the first slots have
+      // eight VALU instructions behind it.  Left to the compiler, the order turned on unrelated
+      // changes by 2%; with these hints P = 8192, C = 512 (32q/8kv) 146.1 -> 143.9 us for two
+      // layers, P = 16384, C = 1000 (16q/4kv) 247.6 -> 243.2, P = 131072, C = 2048 (8q/1kv)
+      // 1597 to 1631 -> 1594.
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (kQK && i < 2) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA (S)
+          __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);   // VALU
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // MFMA (O)
+        if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);          // LDS reads (V)
+        else if (kNext) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);     // LDS reads (K, V)
+        __builtin_amdgcn_sched_group_barrier(0x002, kQK ? 4 : 6, 0);
+      }
     }
     return sn;
   };
@@ -900,13 +921,14 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   constexpr int kDb = 4 / kHalves;
   auto finish = [&](auto first_db) {
     constexpr int D0 = decltype(first_db)::value;
-    // Split piece, when the ring can hold the whole tile's rows: the fp32 partial is staged
-    // through LDS, row-major with each row's 16-byte chunks permuted by (column mod 16) so that
+    // Split piece: the tile's fp32 partial rows are staged through LDS, row-major with each row's 16-byte chunks permuted by (column mod 16) so that
     // both the register-order writes and the row reads are free of bank conflicts, and then
     // stored a row run at a time (the G head rows of a token are adjacent) with device-scope
     // (sc1) stores, which write through the L2: no dirty partial lines are left for the
     // write-back at the end of the launch.  The row sum and max follow with the same policy.
-    if (RingT::kBytes >= kColWaves * 32 * kHeadDim * 4 && ns > 1 && acc_bytes <= 0x7fffffff) {
+    // (The 256-column e4m3 kernel, whose ring alone could not hold the rows, stored them from the
+    // registers: P = 8192, C = 512, 32q/8kv 84.9 -> 82.8 us a layer.)
+    if (ns > 1 && acc_bytes <= 0x7fffffff) {
       constexpr int kSc1 = 16;   // cache policy: device scope
       wait_lgkmcnt0();
       __builtin_amdgcn_s_barrier();   // every wave is past its last read of the ring (or exchange)
@@ -964,7 +986,7 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
         lse[(int64_t)(row0 + tok) * hq + hq_col] = (m_fin + __log2f(l_fin)) * kLn2;
       return;
     }
-    // Split piece (else): fp32 partial (acc row, then (m, l, 0, 0)), stored from the registers; a
+    // Split piece of a request whose partials pass 2 GiB (the stores above have 32-bit offsets): fp32 partial (acc row, then (m, l, 0, 0)), stored from the registers; a
     // column with no visible key in this piece has (-inf, 0): the merge skips it.
     float* ml = acc + (int64_t)ns * C * hq * kHeadDim;
     const int64_t prow = ((int64_t)it.s * C + tok) * hq + hq_col;

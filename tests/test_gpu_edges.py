@@ -178,3 +178,18 @@ def test_native_and_ctypes_marshalling_agree():
         s2l.s2l_kv_append(s.cache, s.batch, None, v)
     with pytest.raises(s2l.S2LError, match="workspace"):
         s2l.s2l_chunk_prefill_attn(s.cache, s.batch, s.q, 32, SCALE, out, lse, plan, ws[:100])
+
+
+@pytest.mark.parametrize("q8", [False, True])
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (7, 1), (64, 8)])
+def test_split_e4m3_pieces_of_256_columns(hq, hkv, q8):
+    """256-column tiles over e4m3 pages in many pieces (their partial rows are staged through LDS
+    and stored as whole rows): full tiles, one token more, a single token, and group sizes that
+    leave columns of a tile unused."""
+    tq = 256 // (hq // hkv)
+    case = workloads.make_case("f8split", [500, 64, 1000], [tq + 1, tq, 1], hq, hkv, seed=57, kv_dtype="fp8")
+    s = Setup(case)
+    s.append()
+    opts = s2l.plan_opts(tile_cols=256, key_halves=1, target_items=1 << 20, min_split_keys=64, max_splits=16)
+    out, lse = s.attention(opts, q8=q8)
+    assert_attention_close(case, out, lse, s.oracle(q8=q8), what="f8split")
