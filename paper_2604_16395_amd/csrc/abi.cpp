@@ -67,7 +67,7 @@ int64_t items_for(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, in
 }
 
 // Piece length of the batch: 0 (no split) when the batch already has at least target_items query
-// tiles; else, and never above max_piece_keys where that is set, the shortest multiple of 64
+// tiles; else (max_piece_keys where that is set and the rule gives twice as much) the shortest multiple of 64
 // keys (at least min_split_keys) for which cutting every request into ceil((P + C) / length) pieces (at most max_splits) gives no
 // more than target_items items, so that one round of workgroups covers the launch and the
 // longest item is as short as that allows.  Item counts fall as the length grows, so the
@@ -89,7 +89,7 @@ int32_t choose_split_keys(int32_t R, const int32_t* P, const int32_t* C, int32_t
     else lo = mid;
   }
   const int32_t keys = (int32_t)(hi * s2l::kKvTile);
-  return o.max_piece_keys > 0 ? std::min(keys, o.max_piece_keys) : keys;
+  return o.max_piece_keys > 0 && keys >= 2 * (int64_t)o.max_piece_keys ? o.max_piece_keys : keys;
 }
 
 // Automatic tile width: 16-column decode tiles when every request fits one (C * G <= 16:

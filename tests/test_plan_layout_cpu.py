@@ -46,3 +46,13 @@ def test_choice_on_short_and_long_ranges():
     for P, C in (([8192], [512]), ([32768] * 8, [512] * 8)):
         info, _ = s2l_plan_host(P, C, 32, 8)
         assert info.tile_cols == 256
+
+
+@pytest.mark.parametrize("P,one_round", [([5000 * (i + 1) for i in range(6)], True), ([16000] * 24, False), ([2047], True)])
+def test_decode_rows_keep_one_round_unless_its_pieces_are_long(P, one_round):
+    """Decode pieces are cut to 4096 keys only where one round of workgroups would leave them at 8192
+    keys or more; else the batch stays within one round."""
+    info, _ = s2l_plan_host(P, [1] * len(P), 32, 8)
+    assert info.tile_cols == 16 and info.num_split_reqs > 0
+    assert (info.num_items <= 256) == one_round
+    assert info.split_keys <= (8192 if one_round else 4096)
