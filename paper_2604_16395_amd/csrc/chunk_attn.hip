@@ -575,10 +575,11 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
       slot_schedule<kQK, kNext>();
     } else {
       // A score MFMA here takes 64 cycles and serves half of the step, so the first slots have
-      // eight VALU instructions behind it.  Left to the compiler, the order turned on unrelated
-      // changes by 2%; with these hints P = 8192, C = 512 (32q/8kv) 146.1 -> 143.9 us for two
-      // layers, P = 16384, C = 1000 (16q/4kv) 247.6 -> 243.2, P = 131072, C = 2048 (8q/1kv)
-      // 1597 to 1631 -> 1594.
+      // eight VALU instructions behind it.  The order the compiler finds by itself turns on unrelated
+      // changes: loading Q and the page ids earlier, before the loop, cost P = 131072, C = 2048
+      // (8q/1kv) 4 us of 772.  With five VALU instructions behind each O MFMA (four: 770 us) that call
+      // takes 765 us, and two layers of P = 8192, C = 512 (32q/8kv) 140.0 us (149.2 in the
+      // compiler's order of then, 141.3 with four), of P = 16384, C = 1000 (16q/4kv) 235.7 (245.1, 237.3).
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         if (kQK && i < 2) {
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // MFMA (O)
         if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);          // LDS reads (V)
         else if (kNext) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);     // LDS reads (K, V)
-        __builtin_amdgcn_sched_group_barrier(0x002, kQK ? 4 : 6, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, kQK ? 5 : 6, 0);
       }
     }
     return sn;
