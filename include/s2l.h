@@ -242,9 +242,10 @@ s2l_status s2l_attn_workspace_bytes(const s2l_batch* batch, int32_t num_q_heads,
  * tiles, each request's key range 0 .. P_r + i_end is split into up to max_splits pieces of
  * >= min_split_keys keys (never more items than target_items in total), so that long
  * prefixes spread over more workgroups (their partial results are merged by
- * s2l_split_reduce); with target_items 0, 16-column tiles of a batch of few tiles whose
- * pieces would be of 8192 keys or more are cut into pieces of at most 4096 keys.  With key_halves = 2 a work item's own range is
- * further halved between two wave groups of its workgroup, merged in LDS.
+ * s2l_split_reduce); with target_items 0, 16-column tiles whose pieces would be of 8192
+ * keys or more are cut into pieces of at most 4096 keys where their items are estimated to end
+ * clearly earlier so.  With key_halves = 2 a work item's own range is further halved between
+ * two wave groups of its workgroup, merged in LDS.
  *   workspace : device, ws_bytes >= s2l_attn_workspace_bytes(...).
  *   info      : HOST out, describes the plan; pass it to the attention calls.
  * The device kernel plans from the device length arrays, sized by the host copies.  Its

@@ -31,12 +31,13 @@ constexpr int kDefaultMaxSplits = 16;
 // Decode tiles, by default.  Pieces down to 256 keys (two 32-key tiles a wave): one row over 2047
 // keys (32q/8kv, bf16) takes 12.7 us a layer with 512-key pieces, 10.9 with 256, 11.6 with 128,
 // where the merge costs more than the shorter pieces save.  At most 32 pieces: one row over
-// 32768 keys takes 38.3 us with 16, 35.7 with 32, 41.6 with 64.  A batch that is split at all is
-// split into pieces of at most 4096 keys, as the longest would end alone (24 requests up to 16K
-// keys, 64q/8kv, fp8: 88.2 us with pieces up to 9984 keys, 82.3 up to 3840, 85.3 up to 1664).
-// That holds where filling one round of workgroups gives pieces of at least twice that; shorter ones
-// stay, as the cap would only add a second, partly filled round (10 rows of a mixed batch, prefixes to
-// 32768 keys: 113 us with one round, 129 with 336 items of up to 4096 keys).
+// 32768 keys takes 38.3 us with 16, 35.7 with 32, 41.6 with 64.  Where filling one round of
+// workgroups gives pieces of at least twice 4096 keys, pieces of at most 4096 are the other choice, as
+// the longest of a round would end alone (24 requests up to 16K keys, 64q/8kv, fp8: 88.2 us with
+// pieces up to 9984 keys, 82.3 up to 3840, 85.3 up to 1664); the host planner takes the one whose
+// items are estimated to end first.  Shorter pieces stay, as the cut would only add a second, partly
+// filled round (10 rows of a mixed batch, prefixes to 32768 keys: 113 us with one round, 129 with 336
+// items of up to 4096 keys).
 constexpr int kDecodeMinSplitKeys = 256;
 constexpr int kDecodeMaxSplits = 32;
 constexpr int kDecodeMaxPieceKeys = 4096;

@@ -80,13 +80,16 @@ def test_decode_tiles_at_their_edges(hq, hkv, kv_dtype):
 
 def test_allocation_free_call_keeps_to_its_scratch():
     """Decode rows whose default plan (pieces of up to 4096 keys) needs more than the library's
-    scratch: the allocation-free call plans them unsplit instead of refusing them."""
-    R, P, hq, hkv, pool = 255, 131071, 16, 1, 64
+    scratch: the allocation-free call plans them unsplit instead of refusing them.  Two rows are three
+    times as long as the others: unsplit they would end long after them (which is what makes the
+    planner cut), and with 255 rows for 256 workgroups one round has no room to split both."""
+    R, hq, hkv, pool = 255, 16, 1, 64
+    P = [131071] * (R - 2) + [3 * 131072 - 1] * 2
     gen = torch.Generator(device=DEV).manual_seed(54)
     rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)
     cache = s2l.PagedKVCache(rnd(pool, hkv, 16, 128), rnd(pool, hkv, 16, 128))
-    tables = torch.randint(0, pool, (R, P // 16 + 1), generator=torch.Generator().manual_seed(54), dtype=torch.int32)
-    batch = s2l.Batch([P] * R, [1] * R, tables.numpy())
+    tables = torch.randint(0, pool, (R, max(P) // 16 + 1), generator=torch.Generator().manual_seed(54), dtype=torch.int32)
+    batch = s2l.Batch(P, [1] * R, tables.numpy())
     assert s2l.s2l_attn_workspace_bytes(batch, hq, hkv) > s2l.NOALLOC_SCRATCH_BYTES
     q, out, ref = rnd(R, hq, 128), torch.empty_like(rnd(R, hq, 128)), torch.empty_like(rnd(R, hq, 128))
     info = s2l.s2l_chunk_prefill_attn_noalloc(cache, batch, q, hq, SCALE, out, None)

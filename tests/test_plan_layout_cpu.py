@@ -56,3 +56,15 @@ def test_decode_rows_keep_one_round_unless_its_pieces_are_long(P, one_round):
     assert info.tile_cols == 16 and info.num_split_reqs > 0
     assert (info.num_items <= 256) == one_round
     assert info.split_keys <= (8192 if one_round else 4096)
+
+
+@pytest.mark.parametrize("P,hq,hkv,cut", [([75125] * 46, 8, 1, False), ([60000] * 25, 64, 8, False),
+                                          ([40000, 30000] + [3000] * 28, 32, 8, True), ([16000] * 24, 32, 8, True)])
+def test_decode_pieces_are_cut_only_where_the_items_end_earlier(P, hq, hkv, cut):
+    """One round of workgroups that is nearly full of equal items (230 of 15026 keys, 200 of 60001)
+    has nothing to gain from a cut to 4096 keys, whose last round is partly filled; one that a few
+    long requests dominate, or that leaves a quarter of the workgroups idle, has."""
+    info, _ = s2l_plan_host(P, [1] * len(P), hq, hkv)
+    one, _ = s2l_plan_host(P, [1] * len(P), hq, hkv, plan_opts(target_items=256))
+    assert one.num_items <= 256 and one.split_keys >= 8192
+    assert info.split_keys == (4096 if cut else one.split_keys)
