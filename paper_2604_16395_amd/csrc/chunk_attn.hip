@@ -922,13 +922,13 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
   constexpr int kDb = 4 / kHalves;
   auto finish = [&](auto first_db) {
     constexpr int D0 = decltype(first_db)::value;
-    // Split piece: the tile's fp32 partial rows are staged through LDS, row-major with each row's 16-byte chunks permuted by (column mod 16) so that
-    // both the register-order writes and the row reads are free of bank conflicts, and then
-    // stored a row run at a time (the G head rows of a token are adjacent) with device-scope
-    // (sc1) stores, which write through the L2: no dirty partial lines are left for the
-    // write-back at the end of the launch.  The row sum and max follow with the same policy.
-    // (The 256-column e4m3 kernel, whose ring alone could not hold the rows, stored them from the
-    // registers: P = 8192, C = 512, 32q/8kv 84.9 -> 82.8 us a layer.)
+    // Split piece: the tile's fp32 partial rows are staged through LDS, row-major with each row's
+    // 16-byte chunks permuted by (column mod 16) so that both the register-order writes and the row
+    // reads are free of bank conflicts, and then stored a row run at a time (the G head rows of a
+    // token are adjacent) with device-scope (sc1) stores, which write through the L2: no dirty partial
+    // lines are left for the write-back at the end of the launch.  The row sum and max follow with the
+    // same policy.  (The 256-column e4m3 kernel, whose ring alone could not hold the rows, stored them
+    // from the registers: P = 8192, C = 512, 32q/8kv 84.9 -> 82.8 us a layer.)
     if (ns > 1 && acc_bytes <= 0x7fffffff) {
       constexpr int kSc1 = 16;   // cache policy: device scope
       wait_lgkmcnt0();
@@ -987,8 +987,9 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
         lse[(int64_t)(row0 + tok) * hq + hq_col] = (m_fin + __log2f(l_fin)) * kLn2;
       return;
     }
-    // Split piece of a request whose partials pass 2 GiB (the stores above have 32-bit offsets): fp32 partial (acc row, then (m, l, 0, 0)), stored from the registers; a
-    // column with no visible key in this piece has (-inf, 0): the merge skips it.
+    // Split piece of a request whose partials pass 2 GiB (the stores above have 32-bit offsets): fp32
+    // partial (acc row, then (m, l, 0, 0)), stored from the registers; a column with no visible key in
+    // this piece has (-inf, 0): the merge skips it.
     float* ml = acc + (int64_t)ns * C * hq * kHeadDim;
     const int64_t prow = ((int64_t)it.s * C + tok) * hq + hq_col;
     float* arow = acc + prow * kHeadDim + 4 * half;
@@ -1095,9 +1096,10 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const PlanHeader* __r
   const int64_t prow0 = (int64_t)tok * hq + h;
   float lb = 0.f, mstar = -INFINITY;
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
-  // a piece without a visible key has m = -inf: weight 0, and its values are not looked at
-  auto add = [&](float m, float l, float wgt, const f32x4& v) {
-    if (m != -INFINITY) {
+  // a piece without a visible key has l = 0, and its values are not looked at; one whose scores hold a
+  // NaN has l = NaN (and m = -inf, weight 0), which makes the row NaN as in an unsplit item
+  auto add = [&](float l, float wgt, const f32x4& v) {
+    if (l != 0.f) {
       lb += wgt * l;
       a += wgt * v;
     }
@@ -1122,7 +1124,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const PlanHeader* __r
       if (s < ns) mstar = fmaxf(mstar, mls[s][0]);
 #pragma unroll
     for (int s = 0; s < kFewPieces; ++s)
-      if (s < ns) add(mls[s][0], mls[s][1], merge_weight(mls[s][0], mstar), v[s]);
+      if (s < ns) add(mls[s][1], merge_weight(mls[s][0], mstar), v[s]);
     store();
     return;
   }
@@ -1147,8 +1149,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const PlanHeader* __r
     for (int k = 0; k < kMergeBatch; ++k)
       if (s0 + k < ns) {
         const int s = s0 + k;
-        add(__shfl(s < 32 ? ml0[0] : ml1[0], s & 31, 32), __shfl(s < 32 ? ml0[1] : ml1[1], s & 31, 32),
-            __shfl(s < 32 ? w0 : w1, s & 31, 32), x[k]);
+        add(__shfl(s < 32 ? ml0[1] : ml1[1], s & 31, 32), __shfl(s < 32 ? w0 : w1, s & 31, 32), x[k]);
       }
   }
   store();

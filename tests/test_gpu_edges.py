@@ -196,3 +196,33 @@ def test_split_e4m3_pieces_of_256_columns(hq, hkv, q8):
     opts = s2l.plan_opts(tile_cols=256, key_halves=1, target_items=1 << 20, min_split_keys=64, max_splits=16)
     out, lse = s.attention(opts, q8=q8)
     assert_attention_close(case, out, lse, s.oracle(q8=q8), what="f8split")
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("cols,halves", [(16, 1), (128, 1), (128, 2), (256, 1)])
+def test_a_nan_key_reaches_every_output_that_sees_it(cols, halves, kv_dtype):
+    """A NaN in one key of one kv head makes the scores, and so every output, of the rows that see it
+    NaN, however their key range is cut: left whole, in the planner's pieces, and in a few and many
+    small ones, where the piece that holds the key has a NaN row sum that the merge must not take
+    for an empty piece.  Earlier rows and the other kv head stay as they are."""
+    hq, hkv, P, C, bad = 4, 2, 700, 5, 702
+    case = workloads.make_case("nan_key", [P, 64], [C, 3], hq, hkv, seed=58, kv_dtype=kv_dtype)
+    s = Setup(case)
+    s.append()
+    plans = [dict(target_items=1), dict(), dict(target_items=1 << 20, min_split_keys=256),
+             dict(target_items=1 << 20, min_split_keys=64, max_splits=64)]
+    for key in (300, bad):
+        for tc in [None] * (cols == 16) + [cols]:
+            clean = [s.attention(s2l.plan_opts(**o, **({} if tc is None else dict(tile_cols=tc, key_halves=halves))))
+                     for o in plans]
+            page, slot = int(case.block_tables[0][key // 16]), key % 16
+            old = s.cache.k_pages[page, 1, slot, 7].clone()
+            s.cache.k_pages[page, 1, slot, 7] = 0x7f if kv_dtype == "fp8" else float("nan")
+            seen = max(0, key - P)
+            for o, (out0, lse0) in zip(plans, clean):
+                out, lse = s.attention(s2l.plan_opts(**o, **({} if tc is None else dict(tile_cols=tc, key_halves=halves))))
+                what = f"key {key}, {o}, {s.plan.num_split_reqs} split requests"
+                assert torch.isnan(out[seen:C, 2:]).all() and torch.isnan(lse[seen:C, 2:]).all(), what
+                for x, y in ((out, out0), (lse, lse0)):
+                    assert torch.equal(x[:, :2], y[:, :2]) and torch.equal(x[C:], y[C:]) and torch.equal(x[:seen], y[:seen]), what
+            s.cache.k_pages[page, 1, slot, 7] = old
