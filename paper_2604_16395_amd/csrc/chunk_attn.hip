@@ -803,14 +803,25 @@ __global__ __launch_bounds__(kColWaves * kHalves * 64, 8 / (kColWaves * kHalves)
       {
         const int t0 = div_g(32 * cw);
         const int nt = min(i1 - i0 - t0, 33);   // at most 32 tokens and a part of one more
-        const i32x4 qrs = sgpr_rsrc(q + ((int64_t)(row0 + i0 + t0) * hq + g * G) * kHeadDim,
-                                    nt > 0 ? ((nt - 1) * hq + G) * kRowBytes : 0);
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem + grp_base + qofs;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
+        const uint16_t* q0 = q + ((int64_t)(row0 + i0 + t0) * hq + g * G) * kHeadDim;
+        const int q_bytes = nt > 0 ? ((nt - 1) * hq + G) * kRowBytes : 0;
+        auto q_offset = [&](int d) -> uint32_t {
           const int c = 4 * d + (lane >> 4), t = div_g(32 * cw + c), h = 32 * cw + c - t * G;
-          const uint32_t voff = (uint32_t)(((t - t0) * hq + h) * kRowBytes + (((lane & 15) ^ (c & 15)) << 4));
-          lds_dma_b128(qrs, voff, __builtin_amdgcn_readfirstlane(lds0 + d * 1024));
+          return (uint32_t)(((t - t0) * hq + h) * kRowBytes + (((lane & 15) ^ (c & 15)) << 4));
+        };
+        if (__builtin_expect((reinterpret_cast<uintptr_t>(q) & 15) == 0, 1)) {
+          const i32x4 qrs = sgpr_rsrc(q0, q_bytes);
+          const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem + grp_base + qofs;
+#pragma unroll
+          for (int d = 0; d < 8; ++d)
+            lds_dma_b128(qrs, q_offset(d), __builtin_amdgcn_readfirstlane(lds0 + d * 1024));
+        } else {   // Q of a view that starts between 16-byte boundaries: through registers
+          for (int d = 0; d < 8; ++d) {
+            const uint32_t voff = q_offset(d);
+            u32x4 x = {0, 0, 0, 0};
+            if (voff < (uint32_t)q_bytes) __builtin_memcpy(&x, reinterpret_cast<const char*>(q0) + voff, 16);
+            *reinterpret_cast<u32x4*>(smem + grp_base + qofs + d * 1024 + lane * 16) = x;
+          }
         }
       }
 #pragma unroll

@@ -226,3 +226,25 @@ def test_a_nan_key_reaches_every_output_that_sees_it(cols, halves, kv_dtype):
                 for x, y in ((out, out0), (lse, lse0)):
                     assert torch.equal(x[:, :2], y[:, :2]) and torch.equal(x[C:], y[C:]) and torch.equal(x[:seen], y[:seen]), what
             s.cache.k_pages[page, 1, slot, 7] = old
+
+
+@pytest.mark.parametrize("offset", [1, 4])
+@pytest.mark.parametrize("cols,halves", [(16, 1), (128, 1), (128, 2), (256, 1)])
+def test_q_and_out_of_a_view_between_16_byte_boundaries(cols, halves, offset):
+    """Contiguous views that start 2 or 8 bytes into a buffer give the bits of aligned tensors, with
+    full tiles, a tile of one token and group sizes that leave columns unused."""
+    for hq, hkv in ((2, 2), (7, 1)):
+        tq = cols // (hq // hkv)
+        case = workloads.make_case("views", [100, 0], [tq + 1, tq], hq, hkv, seed=59)
+        s = Setup(case)
+        s.append()
+        T = case.total_tokens
+        opts = s2l.plan_opts(tile_cols=cols, key_halves=halves)
+        ref, ref_lse = s.attention(opts)
+        n = T * hq * 128
+        q = torch.empty(n + offset, dtype=torch.bfloat16, device=DEV)[offset:].view(T, hq, 128).copy_(s.q)
+        out = torch.full((n + offset,), float("nan"), dtype=torch.bfloat16, device=DEV)[offset:].view(T, hq, 128)
+        lse = torch.empty_like(ref_lse)
+        s2l.s2l_chunk_prefill_attn(s.cache, s.batch, q, hq, SCALE, out, lse, s.plan, s._ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16)) and torch.equal(lse, ref_lse)
