@@ -2,10 +2,12 @@
 loader of libs2l.so.
 
 Loading fails loudly (S2LLibraryMissing) when the built library is absent: there is no
-fallback implementation of any entry point.
+fallback implementation of any entry point.  (Only the native marshalling of the calls' arguments has
+one: ctypes.)
 """
 import ctypes
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # S2L_LIBRARY selects another build of the same library (the host-sanitizer build of
@@ -164,15 +166,28 @@ def call(name, *args):
     return st
 
 
+class _NoBinding:
+    """Stands in for a _binding module that is not there: refuses every call, as the module does with
+    arguments that are not plain, so that the ctypes path takes them all."""
+
+    @staticmethod
+    def _refuse(*_):
+        return None
+
+    append = plan = attn = fused = reduce = _refuse
+
+
 def binding(objects):
     """The native marshalling module (csrc/python/binding.cpp), bound to lib()'s entry points and
-    to `objects`, the types and functions it needs.  Fails loudly when it has not been built."""
+    to `objects`, the types and functions it needs.  Built without Python's headers, or for another
+    interpreter, there is none: said once, in a warning, and a stand-in is returned."""
     handle = lib()
     try:
         from . import _binding
     except ImportError as e:
-        raise S2LLibraryMissing(
-            f"the _binding module is missing ({e}): build it with `python -m paper_2604_16395_amd.build`") from e
+        warnings.warn(f"the native marshalling is missing ({e}): every call goes through ctypes, about 9 us slower; "
+                      "build it with `python -m paper_2604_16395_amd.build`", RuntimeWarning, stacklevel=3)
+        return _NoBinding
     names = ("s2l_kv_append", "s2l_attn_plan", "s2l_chunk_prefill_attn", "s2l_chunk_prefill_attn_q8", "s2l_attn_main",
              "s2l_append_chunk_prefill_attn", "s2l_split_reduce")
     _binding.setup(objects, tuple(ctypes.cast(getattr(handle, n), c_vp).value for n in names))

@@ -1,5 +1,5 @@
 """Build libs2l.so (HIP kernels for gfx950 + the C-ABI layer) and the Python package's native
-argument marshalling (_binding.so, CPython API) in place.
+argument marshalling (_binding.*.so, CPython API; only where Python's headers are) in place.
 
 Usage: python -m paper_2604_16395_amd.build [-v] [--sanitize]
 
@@ -16,6 +16,7 @@ import shutil
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -23,7 +24,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libs2l.so")
-BINDING = os.path.join(PKG, "_binding.so")
+# named for the interpreter it is built for, so that another one does not take it
+BINDING = os.path.join(PKG, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 ARCH = "gfx950"
 
 
@@ -45,6 +47,19 @@ PRELOAD = {"chunk_attn.hip", "decode_attn.hip"}
 PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
+def _run(cmd, verbose):
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    p = subprocess.run(cmd, capture_output=True, text=True)
+    out = "\n".join(l for l in (p.stdout + p.stderr).splitlines()
+                    if "packed-fp32-ops" not in l and l.strip())
+    if p.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{out}")
+    if verbose and out:
+        print(out)
+    return cmd[-1]
+
+
 def build(verbose=False):
     os.makedirs(BUILD, exist_ok=True)
     hipcc = _hipcc()
@@ -56,29 +71,29 @@ def build(verbose=False):
     for src in sorted(glob.glob(os.path.join(CSRC, "*.cpp"))):
         obj = os.path.join(BUILD, os.path.basename(src) + ".o")
         jobs.append([hipcc, *COMMON, "-c", src, "-o", obj])
-    binding = [hipcc, *COMMON, "-shared", "-I", sysconfig.get_paths()["include"],
-               os.path.join(CSRC, "python", "binding.cpp"), "-o", BINDING + ".tmp"]
-
-    def run(cmd):
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        p = subprocess.run(cmd, capture_output=True, text=True)
-        out = "\n".join(l for l in (p.stdout + p.stderr).splitlines()
-                        if "packed-fp32-ops" not in l and l.strip())
-        if p.returncode != 0:
-            raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{out}")
-        if verbose and out:
-            print(out)
-        return cmd[-1]
-
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
-        objs = list(ex.map(run, jobs + [binding]))[:len(jobs)]
-    os.replace(BINDING + ".tmp", BINDING)
+        objs = list(ex.map(lambda cmd: _run(cmd, verbose), jobs))
     tmp = LIB + ".tmp"
-    cmd = [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
-    run(cmd)
+    _run([hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)
+    build_binding(verbose)
     return LIB
+
+
+def build_binding(verbose=False):
+    """The _binding module for the running interpreter.  Without Python's headers there is none (one of an
+    earlier build is removed, as it may follow another s2l.h): the package then marshals all its
+    calls through ctypes, and the library itself does not need it."""
+    headers = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(headers, "Python.h")):
+        warnings.warn(f"no Python.h in {headers}: {os.path.basename(BINDING)} is not built, calls marshal through ctypes")
+        if os.path.exists(BINDING):
+            os.remove(BINDING)
+        return None
+    _run([_hipcc(), *COMMON, "-shared", "-I", headers, os.path.join(CSRC, "python", "binding.cpp"),
+          "-o", BINDING + ".tmp"], verbose)
+    os.replace(BINDING + ".tmp", BINDING)
+    return BINDING
 
 
 SAN = os.path.join(BUILD, "san")

@@ -1,6 +1,9 @@
 """The native argument marshalling takes only what the ctypes path takes (CPU only: no call here
 gets as far as a launch)."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -8,6 +11,8 @@ import torch
 
 import paper_2604_16395_amd as s2l
 from paper_2604_16395_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class _LooksLikeStream:
@@ -36,3 +41,49 @@ def test_objects_that_are_no_streams_are_refused():
     ws = torch.empty(1 << 16, dtype=torch.uint8)
     with pytest.raises(TypeError):
         s2l.s2l_attn_plan(batch, 8, 2, ws, None, _LooksLikeStream())
+
+
+def test_without_the_native_module_every_call_goes_through_ctypes():
+    """An interpreter that the module was not built for gets a warning and the ctypes path, with the
+    same results and errors."""
+    code = """
+import sys, warnings
+import numpy as np, torch
+sys.modules["paper_2604_16395_amd._binding"] = None      # as a missing file: ImportError
+import paper_2604_16395_amd as s2l
+batch = s2l.Batch([16], [4], np.zeros((1, 2), np.int32), device="cpu")
+ws = torch.empty(1 << 16, dtype=torch.uint8)
+row = torch.empty((4, 2, 128), dtype=torch.bfloat16)
+pages = torch.empty((2, 2, 16, 128), dtype=torch.bfloat16)
+q, lse = torch.empty((4, 8, 128), dtype=torch.bfloat16), torch.empty((4, 8))
+cache, info = s2l.PagedKVCache(pages, pages), s2l.s2l_plan_info()
+calls = [lambda: s2l.s2l_attn_plan(batch, 8, 3, ws, None, 0), lambda: s2l.s2l_kv_append(cache, batch, None, row, 0),
+         lambda: s2l.s2l_chunk_prefill_attn(cache, batch, q, 8, 0.1, q, lse, info, ws, 0),
+         lambda: s2l.s2l_append_chunk_prefill_attn(cache, batch, row, row, q, 8, 0.1, q, lse, info, ws, 0),
+         lambda: s2l.s2l_split_reduce(batch, 8, q, lse, info, ws, 0)]
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    for f in calls:
+        try:
+            f()
+        except s2l.S2LError as e:
+            print(e)
+assert [w.category for w in seen] == [RuntimeWarning], seen
+"""
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout + p.stderr
+    said = p.stdout.strip().splitlines()
+    assert len(said) == 5 and all("failed: " in l for l in said), p.stdout
+    assert "not a multiple" in said[0] and "k_new/v_new is NULL" in said[1] and "another batch" in said[2]
+
+
+def test_build_without_python_headers_leaves_the_library(monkeypatch, tmp_path):
+    """No Python.h: no module, a warning, and none of an earlier build is left behind."""
+    from paper_2604_16395_amd import build
+    stale = tmp_path / "_binding.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "BINDING", str(stale))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    with pytest.warns(UserWarning, match="no Python.h"):
+        assert build.build_binding() is None
+    assert not stale.exists()
