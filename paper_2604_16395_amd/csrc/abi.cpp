@@ -9,6 +9,7 @@
 #include <cstddef>
 #include <cstdarg>
 #include <cstdio>
+#include <iterator>
 #include <string>
 #include <vector>
 
@@ -179,17 +180,18 @@ constexpr double kCostMargin = 0.9;
 double layout_cost(int32_t R, const int32_t* P, const int32_t* C, int32_t hq, int32_t hkv, const Layout& y,
                    int32_t split_keys, int32_t max_splits, int32_t cus) {
   const int32_t tq = s2l::tile_tokens(hq / hkv, y.tile_cols);
-  double n = 0, k = 0, kmax = 0, part = 0, tokens = 0;
+  double n = 0, k = 0, longest = 0, part = 0, tokens = 0;
   for (int32_t r = 0; r < R; ++r) {
     if (C[r] <= 0) continue;
     const double ns = s2l::req_splits(P[r], C[r], split_keys, max_splits), nqt = s2l::num_qtiles(C[r], tq);
     const double ends = nqt * P[r] + tq * nqt * (nqt - 1) / 2 + C[r];   // sum of the tiles' key ranges
     n += nqt * ns * hkv;
     k += hkv * (ends / s2l::kKvTile / y.key_halves + 0.5 * nqt * ns);
-    kmax = std::max(kmax, std::ceil(((double)P[r] + C[r]) / (ns * s2l::kKvTile * y.key_halves)));
-    part += (double)s2l::req_part_floats((int32_t)ns, C[r], hq) * 4e-6;
+    longest = std::max(longest, split_keys > 0 ? ((double)P[r] + C[r]) / ns : (double)P[r] + C[r]);
+    if (split_keys > 0) part += (double)s2l::req_part_floats((int32_t)ns, C[r], hq) * 4e-6;
     tokens += C[r];
   }
+  const double kmax = std::ceil(longest / (s2l::kKvTile * y.key_halves));
   const double queue = std::min(1.0, std::max(0.0, n / cus - 0.5));
   const double busy = (y.g * n + y.b * k) / cus + kCostTail * (y.g + y.b * kmax) * queue;
   const double append = std::max(kCostAppend, kCostAppendPerMB * tokens * hkv * s2l::kHeadDim * 8e-6);
@@ -236,17 +238,19 @@ s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, 
   if (!open || frugal || r->tile_cols == s2l::kDecodeTileCols) return S2L_OK;
   const Resolved base = *r;
   double best = INFINITY;
+  bool whole[std::size(kLayouts)] = {};   // layouts whose tiles are enough: no split, so nothing to leave out
   for (int pass = 0; pass < 2; ++pass)   // the default first
     for (const Layout& y : kLayouts)
       for (const bool unsplit : {false, true}) {
         const bool dflt = y.tile_cols == base.tile_cols && y.key_halves == base.key_halves && !unsplit;
-        if (dflt != (pass == 0)) continue;
+        if (dflt != (pass == 0) || (unsplit && whole[&y - kLayouts])) continue;
         Resolved c = base;
         c.tile_cols = y.tile_cols;
         c.key_halves = y.key_halves;
         c.target_items = s2l::items_per_cu(y.tile_cols, y.key_halves) * num_cus;
         c.unsplit = unsplit;
         const int32_t keys = choose_split_keys(R, P, C, hkv, s2l::tile_tokens((int32_t)(hq / hkv), y.tile_cols), c);
+        if (keys == 0) whole[&y - kLayouts] = true;
         const double cost = layout_cost(R, P, C, hq, hkv, y, keys, c.max_splits, num_cus);
         if (dflt) best = kCostMargin * cost;
         else if (cost < best) best = cost, *r = c;
