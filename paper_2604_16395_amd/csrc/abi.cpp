@@ -156,46 +156,87 @@ int32_t auto_tile_cols(int32_t R, const int32_t* C, int32_t hq, int32_t hkv) {
 // part, unused columns and the merge of split partials weigh more in short ones: narrower tiles
 // put two workgroups on a CU or two wave groups on a tile, and no split saves the merge.  Each
 // candidate's time is estimated in us from its items,
-//   max(f + a kmax, (g n + b k) / CUs + t (g + b kmax) clamp(n / CUs - 1/2)) + merge,
-// n items with k 64-key steps in all and kmax in the longest, merge = 3.4 + 0.35 per MB of
-// partials, and taken if it is below 0.9 of the default's.  The constants are a least-squares fit to
-// 721 measured layers (103 batches of 1 to 48 requests, prefixes to 20K, chunks to 2048, five head
-// layouts; root mean square error 6%); over those the choice took 0.91 of the default's time in the
-// geometric mean and was nowhere slower (the fastest of the six candidates: 0.90).
-// Examples, layer time: one 600-token chunk without prefix (32q/8kv) 24.6 -> 16.8 us, P = 20000 and
+//   max(f + a kmax, (g n + b k) / CUs + t (g + b kmax) clamp(n / CUs - 1/2), rounds) + merge,
+// n items with k 64-key steps in all and kmax in the longest, merge linear in the partials' MB.  Of
+// j CUs + 1 items some j + 1 share a CU: rounds is the largest (j + 1) (g + b k') with k' the steps of
+// the (j CUs + 1)-th longest item (266 equal items on 256 CUs take two rounds),
+// and, where a CU holds two items at once, at least 2 (g + b kmax), as the longest may be one of a pair.
+// The plan does not know the cache's element type nor whether the queries will be quantised, so
+// there are two sets of constants, and a candidate is taken if it is below 0.9 of the default's
+// estimate by both (of several the one with the least product of the two).  The bf16 set is a
+// least-squares fit to 721 layers, the e4m3 set to 2886 (350 shapes of 1 to 48 requests, prefixes to
+// 128K, chunks to 2048, eight head layouts, each candidate, with plain and with quantised queries);
+// rounds was shaped on 1400 shapes.  On 300 others the choice takes, against the default, 0.883 of the time in bf16, 0.897 in
+// e4m3 and 0.889 with quantised queries in the geometric mean, and is nowhere slower (the fastest of
+// the six candidates: 0.865, 0.884, 0.873).  With the bf16 set alone and without rounds 2% of the e4m3
+// layers were slower, by up to 1.28 times, where a few more items than CUs put two workgroups on some
+// (P = 22635, C = 532, 64q/1kv, quantised queries: 133 items of 256 columns 447 us, 266 of 128 571).
+// Examples, bf16: one 600-token chunk without prefix (32q/8kv) 24.6 -> 16.8 us, P = 20000 and
 // C = 100 (8q/1kv) 40.1 -> 30.5 us; P = 8192, C = 512 (32q/8kv) stays at 256 columns, four pieces.
 struct Layout {
   int32_t tile_cols, key_halves;
-  double f, a, g, b;
 };
-constexpr Layout kLayouts[] = {
-    {s2l::kMaxTileCols, 1, 4.53, 1.23, 0.78, 1.43},
-    {s2l::kMinTileCols, 1, 3.26, 0.96, 0.0, 0.83},
-    {s2l::kMinTileCols, 2, 5.18, 1.49, 2.98, 1.63},
+constexpr Layout kLayouts[] = {{s2l::kMaxTileCols, 1}, {s2l::kMinTileCols, 1}, {s2l::kMinTileCols, 2}};
+struct CostFit {
+  struct {
+    double f, a, g, b;
+  } layout[std::size(kLayouts)];
+  double tail, merge, merge_per_mb;
+  double base, append;   // whatever the layout: the launches, and the append's latency
 };
-constexpr double kCostTail = 0.52, kCostMerge = 3.4, kCostMergePerMB = 0.35;
-constexpr double kCostBase = 1.2, kCostAppend = 2.2, kCostAppendPerMB = 0.71;   // whatever the layout
+constexpr CostFit kCostFits[] = {
+    {{{4.53, 1.23, 0.78, 1.43}, {3.26, 0.96, 0.0, 0.83}, {5.18, 1.49, 2.98, 1.63}}, 0.52, 3.4, 0.35, 1.2, 2.2},
+    {{{2.55, 1.37, 3.42, 1.38}, {1.64, 1.085, 2.64, 0.75}, {3.32, 1.74, 5.67, 1.585}}, 0.566, 2.92, 0.324, 4.2, 2.86},
+};
+constexpr int kNumFits = (int)std::size(kCostFits);
+constexpr double kCostAppendPerMB = 0.71;
 constexpr double kCostMargin = 0.9;
+constexpr int kMaxRounds = 8;
 
-double layout_cost(int32_t R, const int32_t* P, const int32_t* C, int32_t hq, int32_t hkv, const Layout& y,
-                   int32_t split_keys, int32_t max_splits, int32_t cus) {
-  const int32_t tq = s2l::tile_tokens(hq / hkv, y.tile_cols);
+// The estimates by each set of constants, for layout number `id`.  `order`: the requests, those with the
+// longest items first (by P + C / 2, for any layout), made here when first needed.
+void layout_cost(int32_t R, const int32_t* P, const int32_t* C, int32_t hq, int32_t hkv, int id, int32_t split_keys,
+                 int32_t max_splits, int32_t cus, std::vector<int32_t>* order, double (&cost)[kNumFits]) {
+  const int32_t halves = kLayouts[id].key_halves, tq = s2l::tile_tokens(hq / hkv, kLayouts[id].tile_cols);
   double n = 0, k = 0, longest = 0, part = 0, tokens = 0;
   for (int32_t r = 0; r < R; ++r) {
     if (C[r] <= 0) continue;
     const double ns = s2l::req_splits(P[r], C[r], split_keys, max_splits), nqt = s2l::num_qtiles(C[r], tq);
     const double ends = nqt * P[r] + tq * nqt * (nqt - 1) / 2 + C[r];   // sum of the tiles' key ranges
     n += nqt * ns * hkv;
-    k += hkv * (ends / s2l::kKvTile / y.key_halves + 0.5 * nqt * ns);
+    k += hkv * (ends / s2l::kKvTile / halves + 0.5 * nqt * ns);
     longest = std::max(longest, split_keys > 0 ? ((double)P[r] + C[r]) / ns : (double)P[r] + C[r]);
     if (split_keys > 0) part += (double)s2l::req_part_floats((int32_t)ns, C[r], hq) * 4e-6;
     tokens += C[r];
   }
-  const double kmax = std::ceil(longest / (s2l::kKvTile * y.key_halves));
+  const double kmax = std::ceil(longest / (s2l::kKvTile * halves));
+  double rounds[kNumFits] = {};
+  if (n > cus && n <= kMaxRounds * (double)cus) {   // a last round of more is a small part of the whole
+    if (order->empty()) {
+      for (int32_t r = 0; r < R; ++r)
+        if (C[r] > 0) order->push_back(r);
+      std::sort(order->begin(), order->end(), [&](int32_t a, int32_t b) { return 2 * (int64_t)P[a] + C[a] > 2 * (int64_t)P[b] + C[b]; });
+    }
+    if (s2l::items_per_cu(kLayouts[id].tile_cols, halves) == 2)
+      for (int i = 0; i < kNumFits; ++i)
+        rounds[i] = 2 * (kCostFits[i].layout[id].g + kCostFits[i].layout[id].b * kmax);
+    double items = 0, share = 1;
+    for (const int32_t r : *order) {
+      const double ns = s2l::req_splits(P[r], C[r], split_keys, max_splits), nqt = s2l::num_qtiles(C[r], tq);
+      const double steps = (P[r] + (tq * (nqt - 1) / 2 + C[r] / nqt)) / (ns * s2l::kKvTile * halves);
+      for (items += nqt * ns * hkv; items > share * cus; ++share)
+        for (int i = 0; i < kNumFits; ++i)
+          rounds[i] = std::max(rounds[i], (share + 1) * (kCostFits[i].layout[id].g + kCostFits[i].layout[id].b * steps));
+    }
+  }
   const double queue = std::min(1.0, std::max(0.0, n / cus - 0.5));
-  const double busy = (y.g * n + y.b * k) / cus + kCostTail * (y.g + y.b * kmax) * queue;
-  const double append = std::max(kCostAppend, kCostAppendPerMB * tokens * hkv * s2l::kHeadDim * 8e-6);
-  return kCostBase + append + std::max(y.f + y.a * kmax, busy) + (part > 0 ? kCostMerge + kCostMergePerMB * part : 0);
+  for (int i = 0; i < kNumFits; ++i) {
+    const CostFit& c = kCostFits[i];
+    const auto& y = c.layout[id];
+    const double busy = (y.g * n + y.b * k) / cus + c.tail * (y.g + y.b * kmax) * queue;
+    cost[i] = c.base + std::max(c.append, kCostAppendPerMB * tokens * hkv * s2l::kHeadDim * 8e-6) +
+              std::max({y.f + y.a * kmax, busy, rounds[i]}) + (part > 0 ? c.merge + c.merge_per_mb * part : 0);
+  }
 }
 
 // `frugal` keeps to the rules that need the least workspace: pieces only to fill the GPU, at most 16
@@ -237,23 +278,32 @@ s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, 
   const bool open = !o || (o->target_items == 0 && m == 0 && x == 0 && tc == 0 && kh == 0);
   if (!open || frugal || r->tile_cols == s2l::kDecodeTileCols) return S2L_OK;
   const Resolved base = *r;
-  double best = INFINITY;
+  double best = INFINITY, dflt_cost[kNumFits];
+  std::vector<int32_t> order;
   bool whole[std::size(kLayouts)] = {};   // layouts whose tiles are enough: no split, so nothing to leave out
   for (int pass = 0; pass < 2; ++pass)   // the default first
-    for (const Layout& y : kLayouts)
+    for (int id = 0; id < (int)std::size(kLayouts); ++id)
       for (const bool unsplit : {false, true}) {
+        const Layout& y = kLayouts[id];
         const bool dflt = y.tile_cols == base.tile_cols && y.key_halves == base.key_halves && !unsplit;
-        if (dflt != (pass == 0) || (unsplit && whole[&y - kLayouts])) continue;
+        if (dflt != (pass == 0) || (unsplit && whole[id])) continue;
         Resolved c = base;
         c.tile_cols = y.tile_cols;
         c.key_halves = y.key_halves;
         c.target_items = s2l::items_per_cu(y.tile_cols, y.key_halves) * num_cus;
         c.unsplit = unsplit;
         const int32_t keys = choose_split_keys(R, P, C, hkv, s2l::tile_tokens((int32_t)(hq / hkv), y.tile_cols), c);
-        if (keys == 0) whole[&y - kLayouts] = true;
-        const double cost = layout_cost(R, P, C, hq, hkv, y, keys, c.max_splits, num_cus);
-        if (dflt) best = kCostMargin * cost;
-        else if (cost < best) best = cost, *r = c;
+        if (keys == 0) whole[id] = true;
+        double cost[kNumFits];
+        layout_cost(R, P, C, hq, hkv, id, keys, c.max_splits, num_cus, &order, dflt ? dflt_cost : cost);
+        if (dflt) continue;
+        double product = 1;
+        bool below = true;
+        for (int i = 0; i < kNumFits; ++i) {
+          below = below && cost[i] < kCostMargin * dflt_cost[i];
+          product *= cost[i] / dflt_cost[i];
+        }
+        if (below && product < best) best = product, *r = c;
       }
   return S2L_OK;
 }
