@@ -54,6 +54,7 @@ s2l_status hip_fail(const char* what, hipError_t e) {
 
 struct Resolved {
   int32_t target_items, min_split_keys, max_splits, tile_cols, key_halves;
+  int32_t whole_keys;       // a batch whose key ranges are all of at most so many keys is not split
   int32_t max_piece_keys;   // 0 = none: pieces are only as short as target_items asks for
   bool unsplit;             // key ranges are left whole
 };
@@ -96,7 +97,7 @@ int64_t makespan(int32_t R, const int32_t* P, const int32_t* C, int32_t hkv, int
 }
 
 // Piece length of the batch: 0 (no split) when the batch already has at least target_items query
-// tiles; else the shortest multiple of 64 keys (at least min_split_keys) for which cutting every
+// tiles or no key range of more than whole_keys; else the shortest multiple of 64 keys (at least min_split_keys) for which cutting every
 // request into ceil((P + C) / length) pieces (at most max_splits) gives no more than target_items
 // items, so that one round of workgroups covers the launch and the longest item is as short as
 // that allows.  Item counts fall as the length grows, so the shortest such length is found by
@@ -116,7 +117,7 @@ int32_t choose_split_keys(int32_t R, const int32_t* P, const int32_t* C, int32_t
     tiles += (int64_t)hkv * s2l::num_qtiles(C[r], tq);
     if (C[r] > 0 && (int64_t)P[r] + C[r] > longest) longest = (int64_t)P[r] + C[r];
   }
-  if (tiles == 0 || tiles >= o.target_items || o.unsplit) return 0;
+  if (tiles == 0 || tiles >= o.target_items || o.unsplit || longest <= o.whole_keys) return 0;
   const int64_t lo_keys = s2l::align_up(o.min_split_keys, s2l::kKvTile);
   int64_t lo = lo_keys / s2l::kKvTile, hi = std::max(lo, s2l::ceil_div64(longest, s2l::kKvTile));
   if (items_for(R, P, C, hkv, tq, (int32_t)(lo * s2l::kKvTile), o.max_splits) <= o.target_items) return (int32_t)(lo * s2l::kKvTile);
@@ -272,6 +273,7 @@ s2l_status resolve_opts(const s2l_plan_opts* o, bool need_cus, int32_t num_cus, 
   const int32_t max_splits = decode ? s2l::kDecodeMaxSplits : s2l::kDefaultMaxSplits;
   r->min_split_keys = (int32_t)s2l::align_up(m > 0 ? m : min_keys, s2l::kKvTile);
   r->max_splits = x > 0 ? (x < s2l::kMaxSplitsCap ? x : s2l::kMaxSplitsCap) : max_splits;
+  r->whole_keys = decode && m == 0 ? s2l::kDecodeWholeKeys : 0;
   r->max_piece_keys = decode && (!o || o->target_items == 0)
                           ? std::max<int32_t>(s2l::kDecodeMaxPieceKeys, r->min_split_keys) : 0;
   r->unsplit = false;

@@ -30,7 +30,10 @@ constexpr int kDefaultMinSplitKeys = 512;
 constexpr int kDefaultMaxSplits = 16;
 // Decode tiles, by default.  Pieces down to 256 keys (two 32-key tiles a wave): one row over 2047
 // keys (32q/8kv, bf16) takes 12.7 us a layer with 512-key pieces, 10.9 with 256, 11.6 with 128,
-// where the merge costs more than the shorter pieces save.  At most 32 pieces: one row over
+// where the merge costs more than the shorter pieces save.  That holds from ranges of more than 512
+// keys on: where the longest has no more, the merge's launch costs more than two pieces save (47
+// batches with longest ranges of 257 to 512 keys: 1.10 times the unsplit time in bf16, 1.11 in e4m3;
+// 27 of 513 to 700 keys 0.95 and 1.02), and the batch is left whole.  At most 32 pieces: one row over
 // 32768 keys takes 38.3 us with 16, 35.7 with 32, 41.6 with 64.  Where filling one round of
 // workgroups gives pieces of at least twice 4096 keys, pieces of at most 4096 are the other choice, as
 // the longest of a round would end alone (24 requests up to 16K keys, 64q/8kv, fp8: 88.2 us with
@@ -39,6 +42,7 @@ constexpr int kDefaultMaxSplits = 16;
 // filled round (10 rows of a mixed batch, prefixes to 32768 keys: 113 us with one round, 129 with 336
 // items of up to 4096 keys).
 constexpr int kDecodeMinSplitKeys = 256;
+constexpr int kDecodeWholeKeys = 512;
 constexpr int kDecodeMaxSplits = 32;
 constexpr int kDecodeMaxPieceKeys = 4096;
 constexpr int32_t kPlanMagic = 0x53324c50;  // "S2LP"

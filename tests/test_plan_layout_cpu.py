@@ -77,3 +77,12 @@ def test_choice_is_one_that_e4m3_pages_bear(P, C, hq, hkv):
     6 to 28% there, with plain or quantised queries) keep the default, as the plan serves both."""
     info, _ = s2l_plan_host(P, C, hq, hkv)
     assert info.tile_cols == 256
+
+
+@pytest.mark.parametrize("P,split", [([299] * 8, False), ([511, 40], False), ([512], True), ([300, 700], True)])
+def test_short_decode_rows_are_left_whole(P, split):
+    """Up to 512 keys the merge costs more than two pieces save, unless the caller asks for pieces."""
+    info, _ = s2l_plan_host(P, [1] * len(P), 32, 8)
+    assert info.tile_cols == 16 and (info.num_split_reqs > 0) == split
+    info, _ = s2l_plan_host(P, [1] * len(P), 32, 8, plan_opts(min_split_keys=256))
+    assert info.num_split_reqs > 0
