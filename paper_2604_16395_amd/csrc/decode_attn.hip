@@ -28,8 +28,10 @@
 //     k-steps 2 t and 2 t + 1, widened to bf16 exactly where they are used);
 //   * S^T lands as keys 16 b + 4 q + v of column j in lane (j, q);
 //   * softmax in the exp2 domain against a per-column reference m (the exact max of the
-//     wave's first tile; raised, with O and l rescaled, only if a probability would exceed
-//     2^64), probabilities rounded to bf16, the row sum adding exactly those;
+//     wave's first 64 keys, that is of one e4m3 tile or two bf16 tiles; raised, with O and l
+//     rescaled, at the second of these, and later only if a probability would exceed 2^64: a
+//     reference from 32 keys leaves the largest probabilities further from 1, where they round
+//     exactly, and the result 1% further from the exact one), probabilities rounded to bf16, the row sum adding exactly those;
 //   * V is staged through this wave's private part of the LDS (key-major rows, 16-byte chunks
 //     permuted by 2 (row & 7) so that the transposing reads below hit every bank at most
 //     twice) and read with ds_read_b64_tr_b16 as the A operand of O^T += V^T P^T; the key
@@ -68,14 +70,6 @@ __device__ inline __amdgpu_buffer_rsrc_t page_rsrc(const char* base, int32_t byt
 
 __device__ inline int clamp16i(int x) { return x < 0 ? 0 : (x > 16 ? 16 : x); }
 
-__device__ inline float xmax16(float x) {   // over the four lanes of one column
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
-}
-__device__ inline float xsum16(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
-}
 __device__ inline float dmerge_weight(float m_s, float mstar) {
   return m_s == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_s - mstar);
 }
@@ -261,14 +255,26 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void attn_decode_kernel(
 #pragma unroll
         for (int v = 0; v < 4; ++v) s[b][v] = 16 * b + v > lim ? -INFINITY : s[b][v];
     }
-    if (k == 0) {   // the reference: this column's exact max over the wave's first tile
+    auto tile_max = [&]() {   // this column's, in the log2 domain
       float mx = s[0][0];
 #pragma unroll
       for (int b = 0; b < kPages; ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) mx = fmaxf(mx, s[b][v]);
-      const float t0 = xmax16(mx) * c_log2;
+      return max_of_four(mx) * c_log2;
+    };
+    auto raise = [&](float m_new) {   // O and l hold only earlier tiles
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+      for (int db = 0; db < 8; ++db) o[db] *= alpha;
+      l_run *= alpha;
+      m_run = m_new;
+    };
+    if (k == 0) {   // the reference: this column's exact max over the wave's first 64 keys
+      const float t0 = tile_max();
       m_run = t0 == -INFINITY ? 0.f : t0;
+    } else if (!kFp8 && k == 1) {   // the other 32 of them
+      raise(fmaxf(m_run, tile_max()));
     }
     uint32_t pk[2 * kPages];
     float lsum = 0.f;
@@ -288,19 +294,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void attn_decode_kernel(
     if (__builtin_amdgcn_ballot_w64(lsum > kDOverflow) != 0) {
       // rare: a probability above 2^64 (or inf) in some column; that column's reference
       // becomes this tile's max, O and l (earlier tiles only) are rescaled, P is redone
-      const bool over = xmax16(lsum) > kDOverflow;
-      float mx = s[0][0];
-#pragma unroll
-      for (int b = 0; b < kPages; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) mx = fmaxf(mx, s[b][v]);
-      const float tmax = xmax16(mx) * c_log2;
-      const float m_new = over ? tmax : m_run;
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-#pragma unroll
-      for (int db = 0; db < 8; ++db) o[db] *= alpha;
-      l_run *= alpha;
-      m_run = m_new;
+      const bool over = max_of_four(lsum) > kDOverflow;
+      const float tmax = tile_max();
+      raise(over ? tmax : m_run);
       probs();
     }
     l_run += lsum;
@@ -334,7 +330,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, 2) void attn_decode_kernel(
   }
 
   // merge the four waves' (O, m, l) through LDS, then each wave finishes two dim blocks
-  const float l_col = xsum16(l_run);
+  const float l_col = sum_of_four(l_run);
   const float m_col = l_col > 0.f ? m_run : -INFINITY;   // -inf: no visible key here
   __syncthreads();
   float* xo = reinterpret_cast<float*>(smem);                              // [wave][db][lane][4]

@@ -74,6 +74,22 @@ __device__ inline float sum_with_partner(float x) {
   return x;
 }
 
+// The same over the four lanes l, l ^ 16, l ^ 32, l ^ 48: v_permlane16_swap_b32 first.
+__device__ inline float max_of_four(float x) {
+  float y;
+  __asm__("s_nop 1\n\tv_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1\n\t"
+          "v_max_f32 %0, %0, %1"
+          : "+v"(x), "=&v"(y));
+  return max_with_partner(x);
+}
+__device__ inline float sum_of_four(float x) {
+  float y;
+  __asm__("s_nop 1\n\tv_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1\n\t"
+          "v_add_f32 %0, %0, %1"
+          : "+v"(x), "=&v"(y));
+  return sum_with_partner(x);
+}
+
 // Two words of a lane pair (l, l + 32) exchanged crosswise: the lower lane returns (its a, the
 // upper lane's a), the upper lane (the lower lane's b, its b).
 __device__ inline u32x2 swap_halves(uint32_t a, uint32_t b) {

@@ -248,3 +248,29 @@ def test_q_and_out_of_a_view_between_16_byte_boundaries(cols, halves, offset):
         s2l.s2l_chunk_prefill_attn(s.cache, s.batch, q, hq, SCALE, out, lse, s.plan, s._ws)
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), ref.view(torch.int16)) and torch.equal(lse, ref_lse)
+
+
+def test_decode_reference_covers_the_first_64_keys_of_each_wave():
+    """One-token rows whose weight lies on a single key: within the first 256 keys (64 for each of the
+    four waves) that key sets the reference, its probability is 1 without rounding, and the
+    log-sum-exp is good to fp32 (the score 2^-23 * 30, the other keys' sum 1000 e^-19 * 2^-8).  Rounded
+    against another reference, each of these four scores would be off by 5e-4 or more."""
+    keys, n, hq = [0, 31, 40, 100, 127, 128, 150, 200, 255], 1000, 4
+    cache = s2l.PagedKVCache(torch.zeros((63 * len(keys), 1, 16, 128), dtype=torch.bfloat16, device=DEV),
+                             torch.ones((63 * len(keys), 1, 16, 128), dtype=torch.bfloat16, device=DEV))
+    tables = np.arange(63 * len(keys), dtype=np.int32).reshape(len(keys), 63)
+    for r, j in enumerate(keys):
+        cache.k_pages[63 * r + j // 16, 0, j % 16, 0] = 28.25
+    q = torch.zeros((len(keys), hq, 128), dtype=torch.bfloat16, device=DEV)
+    q[:, :, 0] = torch.tensor([8.0, 8.25, 8.5, 8.75], device=DEV)
+    score = q[:, :, 0].double().cpu() * 28.25 * SCALE
+    exact = score + torch.log1p((n - 1) * torch.exp(-score))
+    batch = s2l.Batch([n - 1] * len(keys), [1] * len(keys), tables)
+    opts = s2l.plan_opts(target_items=1)
+    ws = torch.empty(s2l.s2l_attn_workspace_bytes(batch, hq, 1, opts), dtype=torch.uint8, device=DEV)
+    plan = s2l.s2l_attn_plan(batch, hq, 1, ws, opts)
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:2], device=DEV)
+    s2l.s2l_chunk_prefill_attn(cache, batch, q, hq, SCALE, out, lse, plan, ws)
+    assert plan.tile_cols == 16 and plan.num_split_reqs == 0
+    err = (lse.double().cpu() - exact).abs()
+    assert err.max() < 3e-5, [(j, e.tolist()) for j, e in zip(keys, err)]
