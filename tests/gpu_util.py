@@ -260,7 +260,8 @@ def rescale_excess(setup, opts=None, q8=False, threshold=64.0):
     group's reference, in the log2 domain (scale * log2 e * q.k).  The main kernel's key
     groups are the item's range (or its two halves of whole 64-key tiles with two key groups),
     each with the exact max of its first 32 keys as reference; the decode kernel's are its four
-    waves, wave w taking 64-key tiles w, w + 4, ... with the max of its first tile.  A
+    waves, wave w taking tiles w, w + 4, ... of 32 keys (bf16) or 64 (e4m3), with the max of its first
+    64 keys.  A
     probability above 2^64 sends the kernel through its rescale branch, so an excess above 64
     means the branch runs.  Scores come from the stored keys (fp8: decoded times the scale)
     and the queries as the kernel uses them (q8: quantised per row)."""
@@ -289,24 +290,25 @@ def rescale_excess(setup, opts=None, q8=False, threshold=64.0):
                     continue
                 if info.tile_cols == 16:
                     groups = []
+                    step = 64 if c.kv_dtype == "fp8" else 32
                     for w in range(4):
-                        tiles = list(range(lo + 64 * w, hi, 256))
+                        tiles = [(a, min(a + step, hi)) for a in range(lo + step * w, hi, 4 * step)]
                         if tiles:
-                            groups.append((tiles[0], min(tiles[0] + 64, hi),
-                                           [(a, min(a + 64, hi)) for a in tiles[1:]]))
+                            groups.append((tiles[:64 // step], tiles[64 // step:]))
                 else:
                     nt = -(-(hi - lo) // 64)
                     nt0 = (nt + 1) // 2 if info.key_halves == 2 else nt
                     bounds = [(lo, min(hi, lo + 64 * nt0))]
                     if info.key_halves == 2:
                         bounds.append((lo + 64 * nt0, hi))
-                    groups = [(a, min(a + 32, b), [(min(a + 32, b), b)]) for a, b in bounds if b > a]
-                for ref_lo, ref_hi, later in groups:
+                    groups = [([(a, min(a + 32, b))], [(min(a + 32, b), b)]) for a, b in bounds if b > a]
+                for first, later in groups:
                     for i in range(i0, i1):
                         top = P + i + 1                  # keys 0 .. P + i are visible
-                        if top <= ref_lo:
+                        if top <= first[0][0]:
                             continue
-                        ref = s[i, :, ref_lo:min(ref_hi, top)].max(axis=1)           # [G]
+                        ref = [s[i, :, a:min(b, top)] for a, b in first if min(b, top) > a]
+                        ref = np.concatenate(ref, axis=1).max(axis=1)                # [G]
                         lat = [s[i, :, a:min(b, top)] for a, b in later if min(b, top) > a]
                         if not lat:
                             continue

@@ -2,7 +2,7 @@
 
 The kernels accumulate probabilities against a per-column reference max taken from the first
 keys a key group sees (the main kernel: the first 32 keys of its range; the decode kernel:
-each wave's first 64-key tile).  Only when a later probability would exceed 2^64 do they raise
+each wave's first 64 keys).  Only when a later probability would exceed 2^64 do they raise
 the reference, rescale O and l and redo the sub-block; the result must stay the exact softmax
 of Sec. 2.1 at any score spread.  These inputs plant keys aligned with one query per kv head,
 late in each request, each 72 log2 units above the one before (so the first is far above the
