@@ -159,14 +159,15 @@ def test_native_and_ctypes_marshalling_agree():
             plan = s2l.s2l_attn_plan(s.batch, 32, 8, ws, None, stream)
             s2l.s2l_kv_append(s.cache, s.batch, k, v, stream)
             s2l.s2l_chunk_prefill_attn(s.cache, s.batch, s.q, 32, SCALE, out, lse, plan, ws, stream)
-            res = [out.clone(), lse.clone(), s.cache.k_pages]
             torch.cuda.synchronize()
-            res[0].copy_(out), res[1].copy_(lse)
+            res = [out.clone(), lse.clone(), s.cache.k_pages]
             out.zero_()
+            torch.cuda.synchronize()   # the stream of the fill need not be the one of the calls
             assert s2l.s2l_append_chunk_prefill_attn(s.cache, s.batch, k, v, s.q, 32, SCALE, out, lse, plan, ws, stream)
             torch.cuda.synchronize()
             res.append(out.clone())
             out.zero_()
+            torch.cuda.synchronize()
             s2l.s2l_attn_main(s.cache, s.batch, s.q, 32, SCALE, out, None, plan, ws, stream)
             s2l.s2l_split_reduce(s.batch, 32, out, None, plan, ws, stream)
             torch.cuda.synchronize()
