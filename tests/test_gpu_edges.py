@@ -110,9 +110,10 @@ def test_allocation_free_call_keeps_to_its_scratch():
 
 @pytest.mark.parametrize("R,hkv", [(1, 1), (1, 8), (2, 1), (3, 5), (63, 2), (65, 1), (256, 4), (257, 1), (1024, 1), (1025, 1)])
 def test_device_plan_equals_the_host_plan(R, hkv):
-    """The item records the device wrote (in any order, padding aside) are the host planner's, at
-    the request counts where the plan kernel changes its way: one, a wave, the ranked and binned
-    limit (256), requests kept in LDS (1024)."""
+    """The item records the device wrote (in any order, padding aside) are the host planner's, and so
+    are the request arrays that the merge reads, with partials that tile the planned floats, at the
+    request counts where the plan kernel changes its way: one, a wave, the ranked and binned limit
+    (256), requests kept in LDS (1024)."""
     rng = np.random.default_rng(55 + R)
     P, C = rng.integers(0, 900, R), rng.integers(0, 90, R)
     C[0] = 5
@@ -125,10 +126,14 @@ def test_device_plan_equals_the_host_plan(R, hkv):
         _, items = s2l.s2l_plan_host(P, C, hq, hkv, opts, num_cus=torch.cuda.get_device_properties(0).multi_processor_count,
                                      with_items=True)
         assert len(items) == plan.num_items
-        # records: 64 bytes each after the header and the request arrays (item_off, ns, c, cu, part_off)
-        off = 256 + 4 * (4 * R + 2)
-        off = (-(-off // 8) * 8 + 8 * R + 63) // 64 * 64
-        rec = ws.cpu().numpy()[off:off + 64 * plan.num_items].view(np.int32).reshape(-1, 16)
+        # after the header int32 item_off [R + 1], ns [R], c [R], cu [R + 1], int64 part_off [R]; then
+        # the records, 64 bytes each
+        raw, off = ws.cpu().numpy(), 256 + 4 * (R + 1)
+        ns, c, dev_cu = np.split(raw[off:off + 4 * (3 * R + 1)].view(np.int32), [R, 2 * R])
+        off = -(-(off + 4 * (3 * R + 1)) // 8) * 8
+        part_off = raw[off:off + 8 * R].view(np.int64)
+        off = (off + 8 * R + 63) // 64 * 64
+        rec = raw[off:off + 64 * plan.num_items].view(np.int32).reshape(-1, 16)
         cu = np.concatenate([[0], np.cumsum(C)])
         real = rec[rec[:, 0] >= 0]
         got = sorted(map(tuple, real[:, :8].tolist()))
@@ -136,8 +141,31 @@ def test_device_plan_equals_the_host_plan(R, hkv):
         assert got == sorted(map(tuple, items[items[:, 0] >= 0].tolist()))
         r = real[:, 0]
         assert np.array_equal(real[:, 8], P[r]) and np.array_equal(real[:, 9], C[r]) and np.array_equal(real[:, 10], cu[r])
+        host_ns = np.ones(R, np.int32)
+        host_ns[items[items[:, 0] >= 0, 0]] = items[items[:, 0] >= 0, 7]
+        assert np.array_equal(ns, host_ns) and np.array_equal(c, C) and np.array_equal(dev_cu, cu)
+        assert np.array_equal(np.ascontiguousarray(real[:, 12:14]).view(np.int64)[:, 0], part_off[r])
+        split = np.flatnonzero((ns > 1) & (C > 0))
+        split = split[np.argsort(part_off[split])]
+        ends = np.cumsum(ns[split].astype(np.int64) * C[split] * hq * 132)
+        assert np.array_equal(part_off[split], np.concatenate([[0], ends])[:-1]) and plan.part_floats == (ends[-1] if len(ends) else 0)
+        assert len(split) == plan.num_split_reqs
         pad = rec[rec[:, 0] < 0]
         assert len(pad) == (items[:, 0] < 0).sum() and np.all(pad[:, 0] == -1)
+
+
+@pytest.mark.parametrize("R", [257, 1025])
+def test_split_rows_of_many_requests(R):
+    """Split attention and merge where the plan kernel leaves requests in their order (more than 256)
+    and keeps their offsets in the workspace (more than 1024), in decode and in wide tiles."""
+    rng = np.random.default_rng(R)
+    case = workloads.make_case("many", rng.integers(0, 300, R), rng.integers(0, 4, R), 3, 1, seed=60)
+    s = Setup(case)
+    s.append()
+    for tc in (16, 128):
+        out, lse = s.attention(s2l.plan_opts(tile_cols=tc, target_items=1 << 20, min_split_keys=64))
+        assert s.plan.num_split_reqs > R // 4
+        assert_attention_close(case, out, lse, s.oracle(), what=f"{R} requests, {tc} columns")
 
 
 def test_native_and_ctypes_marshalling_agree():
