@@ -6,12 +6,15 @@ fallback implementation of any entry point.  (Only the native marshalling of the
 one: ctypes.)
 """
 import ctypes
+import importlib.util
 import os
+import sysconfig
 import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # S2L_LIBRARY selects another build of the same library (the host-sanitizer build of
-# `python -m paper_2604_16395_amd.build --sanitize`); by default the in-tree libs2l.so.
+# `python -m paper_2604_16395_amd.build --sanitize`), and a _binding module beside it goes before
+# the in-tree one; by default the in-tree libs2l.so.
 LIB_PATH = os.environ.get("S2L_LIBRARY") or os.path.join(_HERE, "libs2l.so")
 
 S2L_OK, S2L_EINVAL, S2L_ERANGE, S2L_EWORKSPACE, S2L_ENOTSUP, S2L_EHIP = 0, -1, -2, -3, -4, -5
@@ -182,8 +185,14 @@ def binding(objects):
     to `objects`, the types and functions it needs.  Built without Python's headers, or for another
     interpreter, there is none: said once, in a warning, and a stand-in is returned."""
     handle = lib()
+    beside = os.path.join(os.path.dirname(os.path.abspath(LIB_PATH)), "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
     try:
-        from . import _binding
+        if os.environ.get("S2L_LIBRARY") and os.path.exists(beside):
+            spec = importlib.util.spec_from_file_location(__package__ + "._binding", beside)
+            _binding = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(_binding)
+        else:
+            from . import _binding
     except ImportError as e:
         warnings.warn(f"the native marshalling is missing ({e}): every call goes through ctypes, about 9 us slower; "
                       "build it with `python -m paper_2604_16395_amd.build`", RuntimeWarning, stacklevel=3)

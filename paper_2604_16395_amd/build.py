@@ -102,7 +102,8 @@ SAN_FLAGS = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", 
 
 
 def build_sanitized(verbose=False):
-    """Host sources under ASan + UBSan (g++), linked with the device objects of build()."""
+    """Host sources under ASan + UBSan (g++), linked with the device objects of build(), and, where
+    Python's headers are, the native marshalling likewise, beside the library."""
     build(verbose)
     os.makedirs(SAN, exist_ok=True)
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(_hipcc())))
@@ -125,6 +126,13 @@ def build_sanitized(verbose=False):
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    headers = sysconfig.get_paths()["include"]
+    if os.path.exists(os.path.join(headers, "Python.h")):
+        cmd = [gxx, "-std=c++17", "-O1", "-g", "-fPIC", "-shared", *SAN_FLAGS, "-I", headers, "-I", INCLUDE,
+               os.path.join(CSRC, "python", "binding.cpp"), "-o", os.path.join(SAN, os.path.basename(BINDING))]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
     return SAN_LIB
 
 

@@ -43,6 +43,30 @@ def test_objects_that_are_no_streams_are_refused():
         s2l.s2l_attn_plan(batch, 8, 2, ws, None, _LooksLikeStream())
 
 
+def test_plain_arguments_are_marshalled_natively():
+    """Every native function takes plain arguments as far as the library's own checks (which refuse
+    these), and holds no reference to them afterwards."""
+    native = s2l._load_native()
+    batch = s2l.Batch([16, 0], [4, 3], np.zeros((2, 2), np.int32), device="cpu")
+    row, q = (torch.empty((7, h, 128), dtype=torch.bfloat16) for h in (2, 8))
+    lse, ws, scale = torch.empty((7, 8)), torch.empty(1 << 10, dtype=torch.uint8), torch.ones(2)
+    bf16 = torch.empty((2, 2, 32, 128), dtype=torch.bfloat16)      # pages of 32 tokens: not supported
+    caches = [s2l.PagedKVCache(bf16, bf16), s2l.PagedKVCache(bf16.view(torch.uint8)[..., :128].contiguous(),
+                                                             bf16.view(torch.uint8)[..., :128].contiguous(), scale, scale)]
+    info, opts = s2l.s2l_plan_info(), s2l.plan_opts(target_items=4)
+    for cache in caches:
+        args = [cache, batch, row, q, lse, ws, info, opts]
+        before = [sys.getrefcount(a) for a in args]
+        for _ in range(50):
+            assert native.append(cache, batch, row, row, 0) == -4
+            assert native.plan(batch, 8, 3, opts, ws, info, 0) == -1 and native.plan(batch, 8, 3, None, ws, info, 0) == -1
+            assert native.attn(0, cache, batch, q, 8, 0.1, q, lse, info, ws, 0) == -4
+            assert native.fused(cache, batch, q, 8, 0.1, q, None, info, ws, 0, row, row) == (-4, False)
+            assert native.reduce(batch, 8, q, lse, info, ws, 0) == -1
+            assert native.append(cache, batch, row, None, 0) is None and native.attn(3, *args) is None
+        assert [sys.getrefcount(a) for a in args] == before
+
+
 def test_without_the_native_module_every_call_goes_through_ctypes():
     """An interpreter that the module was not built for gets a warning and the ctypes path, with the
     same results and errors."""
@@ -70,7 +94,8 @@ with warnings.catch_warnings(record=True) as seen:
             print(e)
 assert [w.category for w in seen] == [RuntimeWarning], seen
 """
-    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    env = {k: v for k, v in os.environ.items() if k != "S2L_LIBRARY"}   # which may have a module beside it
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
     assert p.returncode == 0, p.stdout + p.stderr
     said = p.stdout.strip().splitlines()
     assert len(said) == 5 and all("failed: " in l for l in said), p.stdout

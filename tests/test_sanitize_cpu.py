@@ -1,5 +1,5 @@
-"""CPU: the host C++ (argument validation, the host planner and its sizing, the scheduler)
-under AddressSanitizer and UndefinedBehaviorSanitizer.  The library is rebuilt with its host
+"""CPU: the host C++ (argument validation, the host planner and its sizing, the scheduler, the
+native marshalling) under AddressSanitizer and UndefinedBehaviorSanitizer.  The library is rebuilt with its host
 sources compiled by g++ with -fsanitize=address,undefined (UB aborts), and the host-side test
 files run against it in a child interpreter with the ASan runtime preloaded.  No GPU call is
 made: those files only validate, plan and schedule."""
@@ -11,7 +11,8 @@ import sys
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-HOST_TESTS = ["tests/test_abi_cpu.py", "tests/test_plan_cpu.py", "tests/test_sched_parity.py"]
+HOST_TESTS = ["tests/test_abi_cpu.py", "tests/test_plan_cpu.py", "tests/test_sched_parity.py", "tests/test_binding_cpu.py",
+              "tests/test_plan_layout_cpu.py"]
 
 
 def _asan_runtime():
@@ -41,11 +42,11 @@ def sanitized_env():
 
 def test_the_sanitized_library_is_the_one_loaded(sanitized_env):
     env, lib = sanitized_env
-    code = ("import paper_2604_16395_amd._lib as L; L.lib(); "
-            "print(any(L.LIB_PATH in l for l in open('/proc/self/maps')), L.LIB_PATH)")
+    code = ("import os, paper_2604_16395_amd as s2l; L = s2l._lib; L.lib(); m = s2l._load_native(); "
+            "print(any(L.LIB_PATH in l for l in open('/proc/self/maps')), L.LIB_PATH, os.path.dirname(m.__file__))")
     p = subprocess.run([sys.executable, "-c", code], env=env, cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert p.returncode == 0, p.stdout + p.stderr
-    assert p.stdout.split() == ["True", lib]
+    assert p.stdout.split() == ["True", lib, os.path.dirname(lib)]
 
 
 def test_host_side_tests_pass_under_asan_and_ubsan(sanitized_env):
