@@ -105,17 +105,25 @@ typedef struct s2l_batch {
   const int32_t* chunk_lens_host;  /* HOST [R], same values                                 */
 } s2l_batch;
 
-/* Tunables of the work partitioner; pass NULL for the defaults. */
+/*
+ * Tunables of the work partitioner; pass NULL for the defaults.  With NULL (or all fields 0) a
+ * batch that is not decode-shaped gets the layout (tile_cols, key_halves) and split whose time
+ * is estimated as clearly least: the rules below, or 128 columns, one or two key groups, with
+ * or without a split.  Any field that is not 0 turns that choice off, and the other fields then
+ * take the values given here (so passing a value that is a default can change the plan).
+ */
 typedef struct s2l_plan_opts {
   int32_t target_items;    /* work items wanted before prefixes are split; 0 = the number   */
                            /* of workgroups the GPU holds at once (CUs x 1 or x 2)          */
   int32_t min_split_keys;  /* smallest key range of a split piece; 0 = 512, or 256 for      */
-                           /* 16-column tiles (rounded to 64)                               */
+                           /* 16-column tiles of a batch with a range of more than 512 keys */
+                           /* (rounded to 64)                                               */
   int32_t max_splits;      /* most pieces per request; 0 = 16, or 32 for 16-column tiles    */
                            /* (at most 64)                                                  */
   int32_t tile_cols;       /* query columns (tokens x heads of one kv head) per work item:  */
-                           /* 128 or 256; 0 = automatic: 256 unless such tiles would be     */
-                           /* less than half full on average (mostly decode-like rows)      */
+                           /* 16, 128 or 256; 0 = automatic: 16 if every request has at     */
+                           /* most 16 (decode-shaped batches), else 256 unless such tiles   */
+                           /* would be less than half full on average, else 128             */
   int32_t key_halves;      /* wave groups per work item, each taking half of its key range: */
                            /* 1 (a 4-wave workgroup per 128 columns, two per CU; 8 waves,   */
                            /* one per CU, for 256) or 2 (128 columns only: an 8-wave        */
@@ -239,13 +247,14 @@ s2l_status s2l_attn_workspace_bytes(const s2l_batch* batch, int32_t num_q_heads,
  * `stream`: per-request arrays and one 64-byte record per work item); reuse it for every
  * layer of the step.  Each request's chunk is cut into query tiles of
  * tile_cols / G tokens x G heads per kv head.  When the batch has fewer than target_items
- * tiles, each request's key range 0 .. P_r + i_end is split into up to max_splits pieces of
- * >= min_split_keys keys (never more items than target_items in total), so that long
- * prefixes spread over more workgroups (their partial results are merged by
- * s2l_split_reduce); with target_items 0, 16-column tiles whose pieces would be of 8192
- * keys or more are cut into pieces of at most 4096 keys where their items are estimated to end
- * clearly earlier so.  With key_halves = 2 a work item's own range is further halved between
- * two wave groups of its workgroup, merged in LDS.
+ * tiles (and the layout chosen without options is not an unsplit one), each request's key
+ * range 0 .. P_r + i_end is split into up to max_splits pieces of >= min_split_keys keys
+ * (never more items than target_items in total), so that long prefixes spread over more
+ * workgroups (their partial results are merged by s2l_split_reduce); with target_items 0,
+ * 16-column tiles whose pieces would be of 8192 keys or more are cut into pieces of at most
+ * 4096 keys where their items are estimated to end clearly earlier so.  With key_halves = 2 a
+ * work item's own range is further halved between two wave groups of its workgroup, merged
+ * in LDS.
  *   workspace : device, ws_bytes >= s2l_attn_workspace_bytes(...).
  *   info      : HOST out, describes the plan; pass it to the attention calls.
  * The device kernel plans from the device length arrays, sized by the host copies.  Its

@@ -390,9 +390,12 @@ void launch_decode_dtype(const AttnLaunch& a, hipStream_t stream) {
   // near-equal length.  With all the unequal items of a batch resident at once, each gets the same
   // share of the memory's rate and the longest end alone; one a CU, they start longest first as
   // CUs fall free: 64 requests of 1K-32K keys (32q/8kv, bf16) 762 -> 676 us a layer, 40 of up to
-  // 8192 (64q/8kv, e4m3) 82.1 -> 74.1 us.  Equal bf16 items take the same either way (64 of 4096
-  // keys 186.0 / 185.3 us); for equal e4m3 items one workgroup has too few bytes in flight (99.4
-  // us for two a CU, 101.1 for one).
+  // 8192 (64q/8kv, e4m3) 82.1 -> 74.1 us, 258 of up to 3303 (16q/1kv, bf16) 54.9 -> 44.6.  For equal
+  // e4m3 items one workgroup has too few bytes in flight (99.4 us for two a CU, 101.1 for one).  Equal
+  // bf16 items of 4096 keys take the same either way (64 rows 186.0 / 185.3 us), but many short ones,
+  // which latency bounds, would gain from two: 433 rows of 372 keys (16q/16kv) 257 us with one, 233 with
+  // two, 922 of up to 30 (32q/8kv) 86 and 51.  Not used: the line between these and the long unequal
+  // ones, by length and by inequality, is not measured.
   const unsigned pad = kFp8 && a.uniform ? 0 : kOneWorkgroupLds - (kFp8 ? 64u : 34u) * 1024;
   const PlanPtrs pv = plan_ptrs(a.workspace, a.dims);
   const int32_t g = a.hq / a.kv.hkv;
