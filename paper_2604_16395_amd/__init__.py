@@ -145,9 +145,10 @@ def _load_native():
     what is wrong with them)."""
     global _native
     if _native is None:
+        # a torch without GPU support lacks the last two: no current stream, so the ctypes path
+        device, raw_stream = (getattr(torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
         _native = _lib.binding((torch.Tensor, PagedKVCache, Batch, s2l_plan_opts, s2l_plan_info, torch.cuda.Stream,
-                                torch.bfloat16, torch.float32, torch.uint8,
-                                torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream))
+                                torch.bfloat16, torch.float32, torch.uint8, torch.cuda.is_initialized, device, raw_stream))
     return _native
 
 

@@ -67,6 +67,25 @@ def test_plain_arguments_are_marshalled_natively():
         assert [sys.getrefcount(a) for a in args] == before
 
 
+def test_a_torch_without_gpu_functions_still_gets_the_library(monkeypatch):
+    """Where torch has no device and stream functions, calls with a stream of their own reach the
+    library, and the others fail where torch is asked for its current stream."""
+    batch = s2l.Batch([16], [4], np.zeros((1, 2), np.int32), device="cpu")
+    ws = torch.empty(1 << 10, dtype=torch.uint8)
+    try:
+        for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+            monkeypatch.delattr(torch._C, name, raising=False)
+        monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+        s2l._native = None
+        with pytest.raises(s2l.S2LError, match="not a multiple"):
+            s2l.s2l_attn_plan(batch, 8, 3, ws, None, 0)
+        assert s2l._load_native().plan(batch, 8, 3, None, ws, s2l.s2l_plan_info(), None) is None
+    finally:   # the module holds what it was set up with
+        monkeypatch.undo()
+        s2l._native = None
+        s2l._load_native()
+
+
 def test_without_the_native_module_every_call_goes_through_ctypes():
     """An interpreter that the module was not built for gets a warning and the ctypes path, with the
     same results and errors."""
